@@ -692,7 +692,8 @@ __device__ __forceinline__ void wave_tile(Lines<P> &a, const SortItem &it, const
 }
 
 template <bool P, class Src, bool SHEAR = false>
-__global__ __launch_bounds__(kWave *kWavesPerGroup) void k_block_sort(Src src)
+__global__ __launch_bounds__(kWave *kWavesPerGroup) __attribute__((amdgpu_waves_per_eu(P ? 1 : 2))) void k_block_sort(
+    Src src)
 {
     src.resolve();
     __shared__ __align__(16) uint32_t lds_all[kWavesPerGroup][kLdsWords];
