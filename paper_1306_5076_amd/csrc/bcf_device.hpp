@@ -776,6 +776,238 @@ __device__ __forceinline__ uint32_t opaque(uint32_t x)
     return x;
 }
 
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+template <class T>
+__device__ __forceinline__ T *uniform(T *p)
+{
+    const uint64_t b = reinterpret_cast<uint64_t>(p);
+    return reinterpret_cast<T *>(((uint64_t)uniform((uint32_t)(b >> 32)) << 32) | uniform((uint32_t)b));
+}
+
+// ------------------------------------- sort of u32 keys, mirrored merge rounds
+//
+// The tile and group sorts of u32 keys.  Every run ascends; a merge of two
+// runs starts by comparing position i of the pair with its mirror 2L - 1 - i
+// (which leaves the lower half's keys in the first run's place and both
+// places bitonic), so no run has to descend and no register is complemented
+// for its direction: the mirror is an address (the partner run is read from
+// the LDS in reverse) or a lane pattern.  The stages of round J are position
+// bits 5+J .. 0; bits 5 .. 0 are registers in BLOCKED layout.
+//   Rounds 1..3 bring lane bits 0..2 together by DPP moves inside eight lanes:
+//     two VALU instructions per key and stage, and no LDS.  (Each round through
+//     the LDS costs two transposes, 512 cycles of the CU's one LDS pipe; the
+//     DPP stages of rounds 1..3 together cost 6 x 64 more VALU instructions on
+//     one of four SIMDs.)
+//   Rounds 4 and 5 use a third layout,
+//       SPLIT    register = p bits 6..10 and p bit 5, lane = p bits 0..4 and p bit 11
+//     which is what the two 32 x 32 block transposes of the half-width scheme
+//     leave without the exchange of quadrants.
+//   Round 6 (p bit 11) takes the half-width transposes to STRIDED and back.  The
+//     upper half of the tile is complemented from the start of the sort (it
+//     ends rounds 1..5 descending), so this round needs no mirror.
+// A wave needs 9 KiB of LDS for all of it, and 64 registers of keys plus what
+// addresses take: four waves fit per SIMD.
+
+// Lane patterns of a DPP move: the partner lane inside four or eight lanes.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B, kDppXor7 = 0x141;
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+
+// One stage against the partner lane: `keep` is 0 in the lanes that take the
+// smaller key and ~0 in those that take the larger one, so that the median of
+// both keys and `keep` is the one to keep.
+template <int CTRL>
+__device__ __forceinline__ void lane_clean(Lines<false> &t, uint32_t keep)
+{
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        t.k[r] = med3(t.k[r], dpp_move<CTRL>(t.k[r]), keep);
+}
+
+// The same against the mirrored register of the partner lane.
+template <int CTRL>
+__device__ __forceinline__ void lane_clean_mirrored(Lines<false> &t, uint32_t keep)
+{
+#pragma unroll
+    for (int r = 0; r < kLine / 2; ++r) {
+        const uint32_t a = t.k[r], b = t.k[kLine - 1 - r];
+        t.k[r] = med3(a, dpp_move<CTRL>(b), keep);
+        t.k[kLine - 1 - r] = med3(b, dpp_move<CTRL>(a), keep);
+    }
+}
+
+// BLOCKED -> SPLIT.  J > 0: with the partner runs of merge round J mirrored:
+// the registers whose bit J - 1 (p bit 5+J) is set take the key of the
+// position with bits 0 .. 4+J inverted.
+template <int J>
+__device__ __forceinline__ void blocked_to_split(uint32_t (&x)[kLine], uint32_t *lds, uint32_t lane)
+{
+    static_assert(J < 6, "the mirror stays inside a half-wave's block");
+    constexpr int H = kLine / 2;
+    uint32_t *m = half_matrix(lds, lane);
+    const uint32_t l = lane & 31;
+    uint32_t *row = static_cast<uint32_t *>(__builtin_assume_aligned(m + kHalfStride * l, 16));
+    uint32_t y[kLine];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int c = 0; c < H; ++c)
+            row[c] = x[H * h + c];
+        wave_lds_fence();
+#pragma unroll
+        for (int r = 0; r < H; ++r) {
+            const bool mirror = J > 0 && ((r >> (J > 0 ? J - 1 : 0)) & 1);
+            if (mirror)
+                y[H * (1 - h) + r] = m[kHalfStride * (r ^ ((1 << (J > 0 ? J - 1 : 0)) - 1)) + (31 - l)];
+            else
+                y[H * h + r] = m[kHalfStride * r + l];
+        }
+        wave_lds_fence();
+    }
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = y[r];
+}
+
+// SPLIT -> BLOCKED.
+__device__ __forceinline__ void split_to_blocked(uint32_t (&x)[kLine], uint32_t *lds, uint32_t lane)
+{
+    half_block_transpose<0, true>(x, lds, lane);
+    half_block_transpose<kLine / 2, true>(x, lds, lane);
+}
+
+// Sort a wave tile of u32 keys: on entry any order (64 keys per lane), on exit
+// sorted in BLOCKED layout.
+__device__ __forceinline__ void sort_tile_keys(Lines<false> &t, uint32_t *lds, uint32_t lane)
+{
+    const uint32_t upper = opaque(0u - (lane >> 5));  // ~0 in the tile's upper half
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        t.k[r] ^= upper;
+    oe_sort_lines<0, kLine - 1>(t);
+    const uint32_t b0 = opaque(0u - (lane & 1)), b1 = opaque(0u - ((lane >> 1) & 1)), b2 = opaque(0u - ((lane >> 2) & 1));
+    lane_clean_mirrored<kDppXor1>(t, b0);
+    half_clean_lines<kLine / 2, -1>(t);
+    lane_clean_mirrored<kDppXor3>(t, b1);
+    lane_clean<kDppXor1>(t, b0);
+    half_clean_lines<kLine / 2, -1>(t);
+    lane_clean_mirrored<kDppXor7>(t, b2);
+    lane_clean<kDppXor2>(t, b1);
+    lane_clean<kDppXor1>(t, b0);
+    half_clean_lines<kLine / 2, -1>(t);
+    blocked_to_split<4>(t.k, lds, lane);
+    half_clean_lines<8, -1>(t);
+    split_to_blocked(t.k, lds, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+    blocked_to_split<5>(t.k, lds, lane);
+    half_clean_lines<16, -1>(t);
+    split_to_blocked(t.k, lds, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+    to_strided_half(t, lds, lane);
+#pragma unroll
+    for (int r = kLine / 2; r < kLine; ++r)
+        t.k[r] = ~t.k[r];
+    half_clean_lines<kLine / 2, -1>(t);
+    to_blocked_half(t, lds, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+}
+
+// Group sort of u32 keys: 8 waves, sub-tiles of 4096 keys, each sorted in
+// BLOCKED layout by its wave; rounds 7..9 merge across the waves through the
+// CROSS layout, half of the group's keys at a time, so that the shared LDS is
+// the waves' own 9 KiB slices side by side (72 KiB: two groups fit a CU).
+// A step stores the keys of one value of a p bit that is a register bit on
+// both sides, at word 2304 (p bits 12..14) + 68 (five of p bits 6..11) + p bits
+// 0..5: lane-consecutive 4-byte accesses and 16-byte accesses of rows 68 words
+// apart, both conflict-free.  In both exchanges a wave writes or reads only its
+// own slice on the BLOCKED / SPLIT side, which saves a barrier.
+constexpr int kKeyGroupWaves = 8;
+
+// BLOCKED p = 4096 wave + 64 lane + r  ->  CROSS (lane = p bits 0..5, wave = p
+// bits 6..8, register = p bits 9..14) for round J = 7..9: the registers whose
+// bit J - 4 (p bit 5+J) is set take the key of the position with bits 0..4+J
+// inverted.  After the exchange of quadrants p bit 11 is register bit 5 on
+// the BLOCKED side and register bit 2 on the CROSS side.
+template <int J>
+__device__ __forceinline__ void keys_to_cross(uint32_t (&x)[kLine], uint32_t *lds, uint32_t lane, uint32_t wave)
+{
+    constexpr int H = kLine / 2;
+    swap_quadrants(x);
+    uint32_t *w = static_cast<uint32_t *>(__builtin_assume_aligned(
+        lds + kHalfLdsWords * wave + kLdsStride * (lane & 31) + H * (lane >> 5), 16));
+    const uint32_t *same = lds + kLdsStride * wave + lane;
+    const uint32_t *mirror = lds + kLdsStride * (kKeyGroupWaves - 1 - wave) + (kWave - 1 - lane);
+    uint32_t y[kLine];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < H; ++r)
+            w[r] = x[H * h + r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kLine; ++r) {
+            const bool up = (r >> (J - 4)) & 1;
+            const int src = up ? r ^ ((1 << (J - 4)) - 1) : r;
+            if (((src >> 2) & 1) == h)
+                y[r] = (up ? mirror : same)[kHalfLdsWords * (src >> 3) + kLdsStride * 8 * (src & 3)];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = y[r];
+}
+
+// CROSS -> SPLIT (p bit 10 is register bit 1 of CROSS and bit 4 of SPLIT).
+__device__ __forceinline__ void cross_to_split(uint32_t (&x)[kLine], uint32_t *lds, uint32_t lane, uint32_t wave)
+{
+    constexpr int H = kLine / 2;
+    uint32_t *w = lds + kLdsStride * wave + lane;
+    const uint32_t *own = lds + kHalfLdsWords * wave + kLdsStride * 16 * (lane >> 5) + (lane & 31);
+    uint32_t y[kLine];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h)
+            __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kLine; ++r)
+            if (((r >> 1) & 1) == h)
+                w[kHalfLdsWords * (r >> 3) + kLdsStride * (8 * (r & 1) + 16 * ((r >> 2) & 1))] = x[r];
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < kLine; ++s)
+            if (((s >> 4) & 1) == h)
+                y[s] = own[kLdsStride * (s & 15) + H * (s >> 5)];
+    }
+    wave_lds_fence();  // the next writes of this slice are the wave's own
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = y[r];
+}
+
+template <int J>
+__device__ __forceinline__ void group_round_keys(Lines<false> &t, uint32_t *lds, uint32_t lane, uint32_t wave)
+{
+    keys_to_cross<J>(t.k, lds, lane, wave);
+    half_clean_lines<(1 << (J - 4)), -1>(t);  // p bits 5+J .. 9
+    cross_to_split(t.k, lds, lane, wave);
+    half_clean_lines<4, -1>(t);  // p bits 8 .. 6
+    split_to_blocked(t.k, lds + kHalfLdsWords * wave, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+}
+
+__device__ __forceinline__ void group_rounds_keys(Lines<false> &t, uint32_t *lds, uint32_t lane, uint32_t wave)
+{
+    group_round_keys<7>(t, lds, lane, wave);
+    group_round_keys<8>(t, lds, lane, wave);
+    group_round_keys<9>(t, lds, lane, wave);
+}
+
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
 // Co-rank (merge-path split) of the stable merge of sorted A and B: the number

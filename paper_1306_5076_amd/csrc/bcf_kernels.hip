@@ -157,6 +157,50 @@ __device__ __forceinline__ void store_tile(const Lines<P> &t, uint32_t *__restri
     }
 }
 
+// Store the first `count` positions of a STRIDED tile (count <= 4096) at dst
+// through a raw buffer resource whose range is those count keys: the memory
+// system drops every store past the range, so no lane is masked per
+// register.  The whole offset of a register (lane + 64 r keys) is passed in the
+// vector offset, the part of the address that the range check covers.
+template <bool NT>
+__device__ __forceinline__ void store_bounded(const uint32_t (&x)[kLine], uint32_t *dst, uint32_t count,
+                                              uint32_t lane)
+{
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dst, (short)0, (int)(count * 4u), 0x00020000);
+#pragma unroll
+    for (int r = 0; r < kLine; ++r) {
+        if ((uint32_t)(kWave * r) >= count)
+            break;  // wave-uniform: rows past the end hold padding only
+        const uint32_t off = opaque(4u * (kWave * r + lane));
+        __builtin_amdgcn_raw_buffer_store_b32(x[r], rs, (int)off, 0, NT ? 2 : 0);
+    }
+}
+template <bool NT>
+__device__ __forceinline__ void store_bounded(const Lines<false> &t, uint32_t *dst, uint32_t count, uint32_t lane)
+{
+    store_bounded<NT>(t.k, dst, count, lane);
+}
+
+// Load `count` keys (at most a tile) into STRIDED layout through a raw buffer
+// resource whose range is those keys: loads past it fetch nothing, and their
+// positions become padding afterwards, so that a ragged tile issues its loads
+// like a full one.  With count == 0 nothing is fetched (src may point past the
+// end of the array).
+__device__ __forceinline__ void load_bounded(Lines<false> &t, const uint32_t *src, uint32_t count, uint32_t lane,
+                                             uint32_t pad)
+{
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(src), (short)0, (int)(count * 4u), 0x00020000);
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        t.k[r] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(4u * (kWave * r + lane)), 0, 0);
+    if (count < (uint32_t)kTile) {
+#pragma unroll
+        for (int r = 0; r < kLine; ++r)
+            t.k[r] = kWave * r + lane < count ? t.k[r] : pad;
+    }
+}
+
 // A work source whose keys go through a key map: the forward map as the block
 // sort loads them, the inverse as the pass that writes the output stores
 // them.  A separate type so that sources of u32 sorts compile without the
@@ -691,53 +735,49 @@ __device__ __forceinline__ void wave_tile(Lines<P> &a, const SortItem &it, const
     store_tile<P>(a, it.kd, it.vd, it.count, lane);
 }
 
+// Wave tiles of key/value sorts, and of keys under the ShearSort ablation.
 template <bool P, class Src, bool SHEAR = false>
-__global__ __launch_bounds__(kWave *kWavesPerGroup) __attribute__((amdgpu_waves_per_eu(P ? 1 : 2))) void k_block_sort(
-    Src src)
+__global__ __launch_bounds__(kWave *kWavesPerGroup) void k_block_sort(Src src)
 {
+    static_assert(P || SHEAR, "u32 keys take k_block_sort_keys");
     src.resolve();
     __shared__ __align__(16) uint32_t lds_all[kWavesPerGroup][kLdsWords];
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t *lds = lds_all[wave];
     const uint32_t G = gridDim.x * kWavesPerGroup;
-    uint32_t t = blockIdx.x * kWavesPerGroup + wave;
-    if (t >= src.ntiles)
-        return;
-    if constexpr (P) {
-        for (; t < src.ntiles; t += G) {
-            const uint32_t ln = opaque(lane);
-            const SortItem it = src.get(t);
-            Lines<P> a;
-            load_tile<P>(a, it.ks, it.count, ln, 0, pad_key(src));
-            wave_tile<P, SHEAR>(a, it, src, t, lds, ln);
-        }
-    } else {
-        Lines<P> a, b;
-        SortItem ia = src.get(t), ib;
-        load_tile<P>(a, ia.ks, ia.count, lane, 0, pad_key(src));
-        for (;;) {
-            uint32_t ln = opaque(lane);
-            const uint32_t tb = t + G;
-            const bool hb = tb < src.ntiles;
-            if (hb) {
-                ib = src.get(tb);
-                load_tile<P>(b, ib.ks, ib.count, ln, 0, pad_key(src));
-            }
-            wave_tile<P, SHEAR>(a, ia, src, t, lds, ln);
-            if (!hb)
-                break;
-            ln = opaque(lane);
-            t = tb + G;
-            const bool ha = t < src.ntiles;
-            if (ha) {
-                ia = src.get(t);
-                load_tile<P>(a, ia.ks, ia.count, ln, 0, pad_key(src));
-            }
-            wave_tile<P, SHEAR>(b, ib, src, tb, lds, ln);
-            if (!ha)
-                break;
-        }
+    for (uint32_t t = blockIdx.x * kWavesPerGroup + wave; t < src.ntiles; t += G) {
+        const uint32_t ln = opaque(lane);
+        const SortItem it = src.get(t);
+        Lines<P> a;
+        load_tile<P>(a, it.ks, it.count, ln, 0, pad_key(src));
+        wave_tile<P, SHEAR>(a, it, src, t, lds, ln);
+    }
+}
+
+// Wave tiles of u32 keys: one wave and 9 KiB of LDS per work-group, 64
+// registers of keys, four waves per SIMD.  Bound by VALU instructions, or by
+// the one wave's chain of them when the tiles are few: 3000 keys 16.8 -> 13.1
+// us, the tiles of a 10,000-segment sort 162 -> 116 us.  The grid strides when
+// it is smaller than the tiles (plans made on the device).
+template <class Src>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_block_sort_keys(Src src)
+{
+    src.resolve();
+    __shared__ __align__(16) uint32_t lds[kHalfLdsWords];
+    for (uint32_t t = blockIdx.x; t < src.ntiles; t += gridDim.x) {
+        const uint32_t lane = opaque(threadIdx.x);
+        const SortItem it = src.get(t);
+        const uint32_t count = uniform(it.count);
+        uint32_t *const dst = uniform(it.kd);
+        Lines<false> a;
+        load_bounded(a, uniform(it.ks), count, lane, pad_key(src));
+        map_tile_in<false>(a, src);
+        sort_tile_keys(a, lds, lane);
+        write_samples<false>(a, src.out_smp, src.pos(t), count, lane);
+        to_strided_half(a, lds, lane);
+        map_tile_out<false>(a, src);
+        store_bounded<false>(a, dst, count, opaque(lane));
     }
 }
 
@@ -798,80 +838,68 @@ struct TableGroupSrc {
     }
 };
 
-// Everything of a group tile after its wave's sub-tile is in registers.
-template <int NW, bool P, class Src>
-__device__ __forceinline__ void group_tile(Lines<P> &t, const SortItem &it, const Src &src, uint32_t g,
-                                           uint32_t *lds, uint32_t lane, uint32_t wave)
-{
-    uint32_t *own = lds + kLdsWords * wave;
-    map_tile_in<P>(t, src);
-    flip(t, wave);  // odd sub-tiles descending
-    sort_tile_blocked<P>(t, own, lane);
-    flip(t, wave);
-    group_rounds<NW, 7>(t, lds, lane, wave);
-    write_samples<P>(t, src.out_smp, src.pos(g, wave), it.count, lane);
-    to_strided(t, own, lane);
-    if constexpr (P) {
-        // group ranks are 4096 * wave + position; wave w stages the values of
-        // its own sub-tile, the LDS is shared by all waves of the group
-        const SortItem i0 = src.get(g, 0);
-        __syncthreads();
-        permute_values_lds(t, i0.vs, src.group_count(g), lds, kTile * wave, it.count, lane,
-                           [] { __syncthreads(); });
-    }
-    map_tile_out<P>(t, src);
-    store_tile<P>(t, it.kd, it.vd, it.count, lane);
-}
-
-// Persistent over group tiles (block b handles groups b, b + grid, ...).  For
-// keys the next group's sub-tile is loaded before the current group is
-// sorted (two tiles of registers); a pairs tile is twice as large, so pairs
-// take one group at a time.  Whether a next group exists is the same for all
-// waves of the block, so every wave reaches the same barriers.
-template <int NW, bool P, class Src>
-__global__ __launch_bounds__(kWave *NW) void k_block_sort_group(Src src)
+// Key/value group tiles, persistent (block b handles groups b, b + grid, ...).
+template <int NW, class Src>
+__global__ __launch_bounds__(kWave *NW) void k_block_sort_group_pairs(Src src)
 {
     src.resolve();
     __shared__ __align__(16) uint32_t lds[NW * kLdsWords];
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    uint32_t g = blockIdx.x;
-    if (g >= src.ngroups)
-        return;
-    if constexpr (P) {
-        for (; g < src.ngroups; g += gridDim.x) {
-            const uint32_t ln = opaque(lane);
-            const SortItem it = src.get(g, wave);
-            Lines<P> t;
-            load_tile<P>(t, it.ks, it.count, ln, wave * kTile, pad_key(src));
-            group_tile<NW, P>(t, it, src, g, lds, ln, wave);
-        }
-    } else {
-        Lines<P> a, b;
-        SortItem ia = src.get(g, wave), ib;
-        load_tile<P>(a, ia.ks, ia.count, lane, 0, pad_key(src));
-        for (;;) {
-            uint32_t ln = opaque(lane);
-            const uint32_t gb = g + gridDim.x;
-            const bool hb = gb < src.ngroups;
-            if (hb) {
-                ib = src.get(gb, wave);
-                load_tile<P>(b, ib.ks, ib.count, ln, 0, pad_key(src));
-            }
-            group_tile<NW, P>(a, ia, src, g, lds, ln, wave);
-            if (!hb)
-                break;
-            ln = opaque(lane);
-            g = gb + gridDim.x;
-            const bool ha = g < src.ngroups;
-            if (ha) {
-                ia = src.get(g, wave);
-                load_tile<P>(a, ia.ks, ia.count, ln, 0, pad_key(src));
-            }
-            group_tile<NW, P>(b, ib, src, gb, lds, ln, wave);
-            if (!ha)
-                break;
-        }
+    uint32_t *own = lds + kLdsWords * wave;
+    for (uint32_t g = blockIdx.x; g < src.ngroups; g += gridDim.x) {
+        const uint32_t ln = opaque(lane);
+        const SortItem it = src.get(g, wave);
+        Lines<true> t;
+        load_tile<true>(t, it.ks, it.count, ln, wave * kTile, pad_key(src));
+        map_tile_in<true>(t, src);
+        flip(t, wave);  // odd sub-tiles descending
+        sort_tile_blocked<true>(t, own, ln);
+        flip(t, wave);
+        group_rounds<NW, 7>(t, lds, ln, wave);
+        write_samples<true>(t, src.out_smp, src.pos(g, wave), it.count, ln);
+        to_strided(t, own, ln);
+        // group ranks are 4096 * wave + position; wave w stages the values of
+        // its own sub-tile, the LDS is shared by all waves of the group
+        const SortItem i0 = src.get(g, 0);
+        __syncthreads();
+        permute_values_lds(t, i0.vs, src.group_count(g), lds, kTile * wave, it.count, ln,
+                           [] { __syncthreads(); });
+        map_tile_out<true>(t, src);
+        store_tile<true>(t, it.kd, it.vd, it.count, ln);
+    }
+}
+
+// Group tiles of u32 keys: 8 waves sort 32768 keys.  Two work-groups share a
+// CU (72 KiB of LDS and at most 128 registers a lane), so one group's loads,
+// barriers and LDS exchanges overlap the other's networks.  Bound by VALU
+// instructions: 6793 per wave of 4096 keys, issued in 94 % of the cycles
+// (SQ_ACTIVE_INST_VALU over wave cycles at four waves), 0 LDS bank conflicts.
+// Measured at 2^26 keys under the profiler: 445 us with one group per CU,
+// complemented runs and 139 KiB of LDS, 300 us so.  The grid strides when it is smaller than the groups; the
+// trip count is the same for all waves, so every wave reaches every barrier.
+template <class Src>
+__global__ __launch_bounds__(kWave *kKeyGroupWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_block_sort_group_keys(
+    Src src)
+{
+    src.resolve();
+    __shared__ __align__(16) uint32_t lds[kKeyGroupWaves * kHalfLdsWords];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t *own = lds + kHalfLdsWords * wave;
+    for (uint32_t g = blockIdx.x; g < src.ngroups; g += gridDim.x) {
+        const uint32_t lane = opaque(threadIdx.x & (kWave - 1));
+        const SortItem it = src.get(g, wave);
+        const uint32_t count = uniform(it.count);
+        uint32_t *const dst = uniform(it.kd);
+        Lines<false> t;
+        load_bounded(t, uniform(it.ks), count, lane, pad_key(src));
+        map_tile_in<false>(t, src);
+        sort_tile_keys(t, own, lane);
+        group_rounds_keys(t, lds, lane, wave);
+        write_samples<false>(t, src.out_smp, src.pos(g, wave), count, lane);
+        to_strided_half(t, own, lane);
+        map_tile_out<false>(t, src);
+        store_bounded<false>(t, dst, count, opaque(lane));
     }
 }
 
@@ -1494,30 +1522,6 @@ __device__ __forceinline__ void merge4_network(Lines<false> &t, uint32_t *lds, u
     half_clean<kLine / 2, -1, false>(t);
     to_blocked_half(t, lds, lane);
     half_clean<kLine / 2, -1, false>(t);
-}
-
-// Store the first `count` positions of a STRIDED tile (count <= 4096) at dst
-// through a raw buffer resource whose range is those count keys: the memory
-// system drops every store past the range, so no lane is masked per
-// register.  The whole offset of a register (lane + 64 r keys) is passed in the
-// vector offset, the part of the address that the range check covers.
-template <bool NT>
-__device__ __forceinline__ void store_bounded(const uint32_t (&x)[kLine], uint32_t *dst, uint32_t count,
-                                              uint32_t lane)
-{
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dst, (short)0, (int)(count * 4u), 0x00020000);
-#pragma unroll
-    for (int r = 0; r < kLine; ++r) {
-        if ((uint32_t)(kWave * r) >= count)
-            break;  // wave-uniform: rows past the end hold padding only
-        const uint32_t off = opaque(4u * (kWave * r + lane));
-        __builtin_amdgcn_raw_buffer_store_b32(x[r], rs, (int)off, 0, NT ? 2 : 0);
-    }
-}
-template <bool NT>
-__device__ __forceinline__ void store_bounded(const Lines<false> &t, uint32_t *dst, uint32_t count, uint32_t lane)
-{
-    store_bounded<NT>(t.k, dst, count, lane);
 }
 
 // Word i (0..3) of the 16 bytes at LDS word w (w a multiple of 4), for a
@@ -2289,6 +2293,23 @@ static uint32_t persistent_groups(K kernel, uint64_t tiles)
     return (uint32_t)(need < (uint64_t)resident ? need : (uint64_t)resident);
 }
 
+template <class K>
+static uint32_t resident_blocks(K kernel, int threads, uint64_t need);
+
+template <class Src>
+constexpr bool kHasDeviceCount = std::is_base_of_v<TableSortSrc, Src> || std::is_base_of_v<TableGroupSrc, Src>;
+
+// Whether a source's count is only known on the device (its launches then
+// stride over the count with a grid sized by the chip).
+template <class Src>
+static bool device_count(const Src &src)
+{
+    if constexpr (kHasDeviceCount<Src>)
+        return src.count_dev != nullptr;
+    else
+        return false;
+}
+
 template <bool P, class Src>
 static hipError_t launch_sort(const Src &src, hipStream_t s, bool shear = false)
 {
@@ -2297,9 +2318,13 @@ static hipError_t launch_sort(const Src &src, hipStream_t s, bool shear = false)
     if (shear) {
         const dim3 grid(persistent_groups(k_block_sort<P, Src, true>, src.ntiles)), block(kWave * kWavesPerGroup);
         hipLaunchKernelGGL((k_block_sort<P, Src, true>), grid, block, 0, s, src);
+    } else if constexpr (P) {
+        const dim3 grid(persistent_groups(k_block_sort<true, Src>, src.ntiles)), block(kWave * kWavesPerGroup);
+        hipLaunchKernelGGL((k_block_sort<true, Src>), grid, block, 0, s, src);
     } else {
-        const dim3 grid(persistent_groups(k_block_sort<P, Src>, src.ntiles)), block(kWave * kWavesPerGroup);
-        hipLaunchKernelGGL((k_block_sort<P, Src>), grid, block, 0, s, src);
+        const uint32_t grid =
+            device_count(src) ? resident_blocks(k_block_sort_keys<Src>, kWave, src.ntiles) : src.ntiles;
+        hipLaunchKernelGGL(k_block_sort_keys<Src>, dim3(grid), dim3(kWave), 0, s, src);
     }
     return hipGetLastError();
 }
@@ -2381,9 +2406,16 @@ static hipError_t launch_group_src(const Src &src, hipStream_t s)
 {
     if (src.ngroups == 0)
         return hipSuccess;
-    // one group per CU fits the LDS (NW * 16.6 KiB); persistent over the groups
-    const uint32_t groups = src.ngroups < cu_count() ? src.ngroups : cu_count();
-    hipLaunchKernelGGL((k_block_sort_group<NW, P, Src>), dim3(groups), dim3(kWave * NW), 0, s, src);
+    if constexpr (P) {
+        // one wave per SIMD; persistent over the groups
+        const uint32_t groups = src.ngroups < cu_count() ? src.ngroups : cu_count();
+        hipLaunchKernelGGL((k_block_sort_group_pairs<NW, Src>), dim3(groups), dim3(kWave * NW), 0, s, src);
+    } else {
+        static_assert(NW == kKeyGroupWaves, "waves of a key group");
+        const uint32_t grid =
+            device_count(src) ? resident_blocks(k_block_sort_group_keys<Src>, kWave * NW, src.ngroups) : src.ngroups;
+        hipLaunchKernelGGL(k_block_sort_group_keys<Src>, dim3(grid), dim3(kWave * NW), 0, s, src);
+    }
     return hipGetLastError();
 }
 
