@@ -329,7 +329,11 @@ uint32_t bcf_run_keys(int pairs);
  * pass merges the final two runs if needed: 2^11 runs take 6 passes instead
  * of 11.  Each merge pass finds its work split by reading
  * O(log n) key samples and keys, in a small launch before it or (see
- * bcf_tuning.fused_partition) in the merge kernel. */
+ * bcf_tuning.fused_partition) in the merge kernel.
+ * Under the default tuning, sorts of at most 2^19 keys or 2^20 pairs merge
+ * up to 16 runs of 4096 per pass by ranks instead, in at most two passes; the
+ * count returned for them is that of the binary or four-way passes they
+ * replace, as for an explicit merge_fan_in. */
 uint32_t bcf_sort_passes(uint64_t n, int pairs);
 
 /*

@@ -235,6 +235,41 @@ std::vector<uint32_t> sort_fan_ins(bool pairs, uint64_t n, const Tuning &tu)
     return fi;
 }
 
+// Small sorts under the default tuning: tiles of 4096 sorted by four waves each,
+// then one or two passes that merge up to 16 runs each by ranks, as long as the
+// work of the ranks (which grows with the fan-ins) costs less than the launches
+// it saves.  Measured, ranks against wave tiles and binary passes (keys) or
+// four-way passes (pairs): keys 2^16 18.6 / 42.0 us, 2^18 30.6 / 57.2, 2^19
+// 56.5 / 65.1, 786,432 83.0 / 79.3; pairs 2^16 26.8 / 90.9 us, 2^18 39.7 /
+// 123.7, 2^20 117.7 / 153.1 (16 runs of 16 tiles each are the most two passes take).
+constexpr uint64_t kSmallMaxKeys = 1ull << 19;
+constexpr uint64_t kSmallMaxPairs = 1ull << 20;
+
+bool sort_is_small(bool pairs, uint64_t n, const Tuning &tu)
+{
+    return n <= (pairs ? kSmallMaxPairs : kSmallMaxKeys) && tu.block_sort == 0 && tu.merge_fan_in == 0 &&
+           tu.merge_variant == 3 && tu.sampled_partition && tu.fused_partition && tu.tile_samples;
+}
+
+// Fan-ins of the rank passes over `runs` (at most 256) runs of 4096: one pass for up
+// to 16 runs, else two whose fan-ins are as even as they can be (an element's
+// cost grows with the sum of both).
+uint32_t rank_fan_ins(uint64_t runs, uint32_t (&fan)[2])
+{
+    if (runs <= 1)
+        return 0;
+    if (runs <= 16) {
+        fan[0] = (uint32_t)runs;
+        return 1;
+    }
+    uint32_t f = 5;
+    while ((uint64_t)f * f < runs)
+        ++f;
+    fan[0] = f;
+    fan[1] = (uint32_t)((runs + f - 1) / f);
+    return 2;
+}
+
 // kind 0: u32 keys; 1 int32, 2 float: keys are mapped in order to u32 as the
 // block sort loads them and mapped back as the last pass stores them.
 bcf_status sort_impl(bool pairs, const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
@@ -245,8 +280,11 @@ bcf_status sort_impl(bool pairs, const uint32_t *kin, const uint32_t *vin, uint3
     const uint64_t tiles = tiles_of(n);
     const Tuning tu = tuning();
     const uint64_t run0 = sort_run_keys(pairs, n, tu);  // sorted run length after the block sort
-    const std::vector<uint32_t> fan_in = sort_fan_ins(pairs, n, tu);
-    const uint32_t passes = (uint32_t)fan_in.size();
+    const bool small = sort_is_small(pairs, n, tu);
+    uint32_t rank_fan[2];
+    const uint32_t rank_passes = small ? rank_fan_ins(tiles, rank_fan) : 0;
+    const std::vector<uint32_t> fan_in = small ? std::vector<uint32_t>() : sort_fan_ins(pairs, n, tu);
+    const uint32_t passes = small ? rank_passes : (uint32_t)fan_in.size();
     // temp: ping-pong keys [, values], one split per merge tile, two sets of
     // key samples (each pass reads one set and writes the other), then (keys)
     // the cut list of a four-way pass.  The layout does not depend on the
@@ -290,6 +328,22 @@ bcf_status sort_impl(bool pairs, const uint32_t *kin, const uint32_t *vin, uint3
     const KeyMap fwd = key_map(kind, false), inv = key_map(kind, true);
     // the pass that writes the output stores through the inverse map
     auto out_map = [&](uint32_t j) { return j == passes ? inv : KeyMap{}; };
+    if (small) {
+        {
+            ProfScope p(kname_block_sort(pairs, false), s, 2.0 * elem_bytes * n);
+            BCF_TRY(dev_status(launch_tile_sort(pairs, kin, vin, kbuf(0), pairs ? vbuf(0) : nullptr, n,
+                                                passes ? sample_set(0) : none, s, fwd, out_map(0))));
+        }
+        uint64_t run = kTile;
+        for (uint32_t j = 1; j <= passes; run *= rank_fan[j - 1], ++j) {
+            ProfScope p(pairs ? "rank_merge_pairs" : "rank_merge_keys", s, 2.0 * elem_bytes * n);
+            BCF_TRY(dev_status(launch_rank_merge(kbuf(j - 1), pairs ? vbuf(j - 1) : nullptr, kbuf(j),
+                                                 pairs ? vbuf(j) : nullptr, n, run, rank_fan[j - 1],
+                                                 sample_set((j - 1) & 1), j < passes ? sample_set(j & 1) : none, s,
+                                                 out_map(j))));
+        }
+        return BCF_OK;
+    }
     {
         ProfScope p(kname_block_sort(pairs, false), s, 2.0 * elem_bytes * n);
         const SampleSet smp = (passes && sampled) ? sample_set(0) : none;

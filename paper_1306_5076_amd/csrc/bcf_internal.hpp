@@ -92,6 +92,16 @@ hipError_t launch_block_sort_shear_group(const uint32_t *kin, uint32_t *kout, ui
 hipError_t launch_block_sort_regular(bool pairs, bool shear, const uint32_t *kin, const uint32_t *vin,
                                      uint32_t *kout, uint32_t *vout, uint64_t n, SampleSet out_smp,
                                      hipStream_t s, KeyMap in_map = {}, KeyMap out_map = {});
+// Wave tiles' work by work-groups of four waves, 16 elements per lane (merge
+// rounds; same runs and samples): the block sort of small sorts.
+hipError_t launch_tile_sort(bool pairs, const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
+                            uint64_t n, SampleSet out_smp, hipStream_t s, KeyMap in_map = {}, KeyMap out_map = {});
+// One pass that merges groups of `fan` (2..16) runs of `run` keys (a multiple of
+// 4096, at most 131072) by ranks; stable, values move along when vsrc is set.
+// Reads the 64-key block samples of its input and writes those of its output.
+hipError_t launch_rank_merge(const uint32_t *ksrc, const uint32_t *vsrc, uint32_t *kdst, uint32_t *vdst, uint64_t n,
+                             uint64_t run, uint32_t fan, SampleSet in_smp, SampleSet out_smp, hipStream_t s,
+                             KeyMap out_map = {});
 // A merge pass is two launches: with partition = true the split of every
 // tile is written to `splits` (one u32 per tile of the pass); with
 // partition = false the tiles are merged using those splits.

@@ -2272,6 +2272,12 @@ __global__ void k_check_runs(const uint32_t *__restrict__ keys, const uint64_t *
     }
 }
 
+}  // namespace bcf
+
+#include "bcf_small.hpp"
+
+namespace bcf {
+
 // ------------------------------------------------------------------ launchers
 
 // Work-groups of a persistent launch: enough to fill every CU at the
@@ -2386,6 +2392,52 @@ hipError_t launch_block_sort_regular(bool pairs, bool shear, const uint32_t *kin
         return pairs ? launch_sort<true>(ms, s) : launch_sort<false>(ms, s);
     }
     return pairs ? launch_sort<true>(src, s, shear) : launch_sort<false>(src, s, shear);
+}
+
+template <bool P, class Src>
+static hipError_t launch_tile(const Src &src, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_tile_sort<P, Src>), dim3(src.ntiles), dim3(kSmallThreads), 0, s, src);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_sort(bool pairs, const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
+                            uint64_t n, SampleSet out_smp, hipStream_t s, KeyMap in_map, KeyMap out_map)
+{
+    if (n == 0)
+        return hipSuccess;
+    const RegularSortSrc src{kin, pairs ? vin : nullptr, kout, pairs ? vout : nullptr, n,
+                             (uint32_t)((n + kTile - 1) / kTile), out_smp};
+    if (in_map.sign || out_map.sign) {
+        const Mapped<RegularSortSrc> ms{src, in_map, out_map};
+        return pairs ? launch_tile<true>(ms, s) : launch_tile<false>(ms, s);
+    }
+    return pairs ? launch_tile<true>(src, s) : launch_tile<false>(src, s);
+}
+
+hipError_t launch_rank_merge(const uint32_t *ksrc, const uint32_t *vsrc, uint32_t *kdst, uint32_t *vdst, uint64_t n,
+                             uint64_t run, uint32_t fan, SampleSet in_smp, SampleSet out_smp, hipStream_t s,
+                             KeyMap out_map)
+{
+    const bool pairs = vsrc != nullptr;
+    // the searches read the samples of the input; runs start at multiples of 4096
+    if (n == 0 || run % kTile != 0 || run > kRankMaxRun || fan < 2 || fan > kRankMaxFan || in_smp.f == nullptr ||
+        pairs != (vdst != nullptr))
+        return hipErrorInvalidValue;
+    const RankSrc src{ksrc, vsrc, kdst, vdst, n, run, fan, in_smp.f, out_smp.f, out_map};
+    const uint64_t runs = (n + run - 1) / run;
+    if (n > kMaxKey || runs > 65535)
+        return hipErrorInvalidValue;
+    const dim3 grid((uint32_t)(run / kRankChunk), (uint32_t)runs), block(kRankChunk);
+    if (pairs && out_map.sign)
+        hipLaunchKernelGGL((k_rank_merge<true, true>), grid, block, 0, s, src);
+    else if (pairs)
+        hipLaunchKernelGGL((k_rank_merge<true, false>), grid, block, 0, s, src);
+    else if (out_map.sign)
+        hipLaunchKernelGGL((k_rank_merge<false, true>), grid, block, 0, s, src);
+    else
+        hipLaunchKernelGGL((k_rank_merge<false, false>), grid, block, 0, s, src);
+    return hipGetLastError();
 }
 
 static uint32_t cu_count()
