@@ -917,6 +917,94 @@ __device__ __forceinline__ void sort_tile_keys(Lines<false> &t, uint32_t *lds, u
     half_clean_lines<kLine / 2, -1>(t);
 }
 
+// The same sort of a wave tile of key/value elements: a stage between lanes takes
+// two moves, a comparison and two selects per element (five VALU instructions
+// against two for a key), which still undercuts the two transposes of both
+// 32-bit halves that a round through the LDS costs.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x)
+{
+    const uint64_t b = bits_of(x);
+    const uint32_t hi = dpp_move<CTRL>((uint32_t)(b >> 32)), lo = dpp_move<CTRL>((uint32_t)b);
+    return elem_of(((uint64_t)hi << 32) | lo);
+}
+
+// The smaller of x and y, or the larger; equal elements are alike in every bit.
+__device__ __forceinline__ double keep_elem(double x, double y, bool larger) { return ((x < y) != larger) ? x : y; }
+
+template <int CTRL>
+__device__ __forceinline__ void lane_clean(Lines<true> &t, bool larger)
+{
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        t.e[r] = keep_elem(t.e[r], dpp_move<CTRL>(t.e[r]), larger);
+}
+
+template <int CTRL>
+__device__ __forceinline__ void lane_clean_mirrored(Lines<true> &t, bool larger)
+{
+#pragma unroll
+    for (int r = 0; r < kLine / 2; ++r) {
+        const double a = t.e[r], b = t.e[kLine - 1 - r];
+        t.e[r] = keep_elem(a, dpp_move<CTRL>(b), larger);
+        t.e[kLine - 1 - r] = keep_elem(b, dpp_move<CTRL>(a), larger);
+    }
+}
+
+template <int J>
+__device__ __forceinline__ void blocked_to_split(double (&x)[kLine], uint32_t *lds, uint32_t lane)
+{
+    uint32_t hi[kLine], lo[kLine];
+    split_halves(x, hi, lo);
+    blocked_to_split<J>(hi, lds, lane);
+    blocked_to_split<J>(lo, lds, lane);
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+}
+
+__device__ __forceinline__ void split_to_blocked(double (&x)[kLine], uint32_t *lds, uint32_t lane)
+{
+    uint32_t hi[kLine], lo[kLine];
+    split_halves(x, hi, lo);
+    split_to_blocked(hi, lds, lane);
+    split_to_blocked(lo, lds, lane);
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+}
+
+__device__ __forceinline__ void sort_tile_pairs(Lines<true> &t, uint32_t *lds, uint32_t lane)
+{
+    flip(t, lane >> 5);
+    oe_sort_lines<0, kLine - 1>(t);
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    lane_clean_mirrored<kDppXor1>(t, b0);
+    half_clean_lines<kLine / 2, -1>(t);
+    lane_clean_mirrored<kDppXor3>(t, b1);
+    lane_clean<kDppXor1>(t, b0);
+    half_clean_lines<kLine / 2, -1>(t);
+    lane_clean_mirrored<kDppXor7>(t, b2);
+    lane_clean<kDppXor2>(t, b1);
+    lane_clean<kDppXor1>(t, b0);
+    half_clean_lines<kLine / 2, -1>(t);
+    blocked_to_split<4>(t.e, lds, lane);
+    half_clean_lines<8, -1>(t);
+    split_to_blocked(t.e, lds, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+    blocked_to_split<5>(t.e, lds, lane);
+    half_clean_lines<16, -1>(t);
+    split_to_blocked(t.e, lds, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+    to_strided_half(t, lds, lane);
+#pragma unroll
+    for (int r = kLine / 2; r < kLine; ++r)
+        t.e[r] = elem_of(bits_of(t.e[r]) ^ kPayloadMask);
+    half_clean_lines<kLine / 2, -1>(t);
+    to_blocked_half(t, lds, lane);
+    half_clean_lines<kLine / 2, -1>(t);
+}
+
 // Group sort of u32 keys: 8 waves, sub-tiles of 4096 keys, each sorted in
 // BLOCKED layout by its wave; rounds 7..9 merge across the waves through the
 // CROSS layout, half of the group's keys at a time, so that the shared LDS is
@@ -1001,11 +1089,17 @@ __device__ __forceinline__ void group_round_keys(Lines<false> &t, uint32_t *lds,
     half_clean_lines<kLine / 2, -1>(t);
 }
 
-__device__ __forceinline__ void group_rounds_keys(Lines<false> &t, uint32_t *lds, uint32_t lane, uint32_t wave)
+// The rounds that a group of `count` keys needs: a run that reaches the last key
+// is merged with padding only.
+__device__ __forceinline__ void group_rounds_keys(Lines<false> &t, uint32_t *lds, uint32_t lane, uint32_t wave,
+                                                  uint32_t count)
 {
-    group_round_keys<7>(t, lds, lane, wave);
-    group_round_keys<8>(t, lds, lane, wave);
-    group_round_keys<9>(t, lds, lane, wave);
+    if (count > kTile)
+        group_round_keys<7>(t, lds, lane, wave);
+    if (count > 2 * kTile)
+        group_round_keys<8>(t, lds, lane, wave);
+    if (count > 4 * kTile)
+        group_round_keys<9>(t, lds, lane, wave);
 }
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }

@@ -281,41 +281,83 @@ __device__ __forceinline__ void map_tile_out(Lines<P> &t, const KeyMap &m)
 typedef __attribute__((address_space(1))) const void global_cvoid;
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Value step of a block sort (pairs): the tile is sorted, in STRIDED layout,
-// and every element's rank is its input position in [0, count) (padding
-// ranks are larger).  The values of those `count` input positions are staged
-// in LDS (`vals`, coalesced global reads, conflict-free consecutive LDS
-// words) and each element is repacked as its key and the value read from LDS
-// at its rank.  Callers separate this from other LDS use by the fence or
-// barrier `sync`.
-template <class Sync>
-__device__ __forceinline__ void permute_values_lds(Lines<true> &t, const uint32_t *__restrict__ vsrc,
-                                                   uint32_t count, uint32_t *vals, uint32_t stage_off,
-                                                   uint32_t stage_count, uint32_t lane, const Sync &sync)
+// Load `count` keys (at most a tile) into STRIDED key/value elements of ranks
+// rank0 + p, padded; through a raw buffer resource as for keys.  All loads are
+// issued before the first conversion, and the conversions stay one register
+// at a time: both keep the tile at two waves per SIMD.
+template <class Src>
+__device__ __forceinline__ void load_elems(Lines<true> &t, const uint32_t *ksrc, uint32_t count, uint32_t lane,
+                                           uint32_t rank0, const Src &src)
 {
-    // stage input positions [stage_off, stage_off + stage_count) of this wave
-    // with direct global-to-LDS loads (lanes past the end re-read the first
-    // position; their LDS words are never read).  A wave with nothing to
-    // stage (a group tile's sub-tile past the end of the input, where src
-    // points past the end of the array) issues no load.
-    const uint32_t *src = vsrc + stage_off;
-    if (stage_count != 0) {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(ksrc), (short)0, (int)(count * 4u), 0x00020000);
+    const uint32_t pad = pad_key(src);
+    uint32_t key[kLine];
 #pragma unroll
-        for (int r = 0; r < kLine; ++r) {
-            const uint32_t p = kWave * r + lane;
-            __builtin_amdgcn_global_load_lds((global_cvoid *)(src + (p < stage_count ? p : 0u)),
-                                             (lds_void *)(vals + stage_off + kWave * r), 4, 0, 0);
-        }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    sync();
+    for (int r = 0; r < kLine; ++r)
+        key[r] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(4u * (kWave * r + lane)), 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int r = 0; r < kLine; ++r) {
-        const uint32_t rank = elem_rank(t.e[r]);
-        const uint32_t v = rank < count ? vals[rank] : 0u;
-        t.e[r] = make_out(elem_key(t.e[r]), v);
+        const uint32_t p = kWave * r + lane;
+        uint32_t k = p < count ? key[r] : pad;
+        if constexpr (Src::kMapped)
+            k = map_key(k, src.in_map.sign, src.in_map.rest, src.in_map.inverse);
+        t.e[r] = make_elem(k, p < count ? rank0 + p : kPadRank);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    sync();
+}
+
+// The values of `count` (at most a tile) consecutive input positions into LDS
+// words at `vals`, by direct global-to-LDS loads that the caller waits for.
+// With count == 0 (vsrc may point past the end of the array) nothing is loaded.
+__device__ __forceinline__ void stage_values(const uint32_t *__restrict__ vsrc, uint32_t count, uint32_t *vals,
+                                             uint32_t lane)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the wave's reads of the LDS words before
+    if (count == (uint32_t)kTile) {
+#pragma unroll
+        for (int r = 0; r < kLine; ++r)
+            __builtin_amdgcn_global_load_lds((global_cvoid *)(vsrc + kWave * r + lane), (lds_void *)(vals + kWave * r), 4,
+                                             0, 0);
+    } else {
+#pragma unroll 1
+        for (uint32_t i = 0; i < count; i += kWave)  // lanes past the end read a word that is not used
+            __builtin_amdgcn_global_load_lds((global_cvoid *)(vsrc + (i + lane < count ? i + lane : 0u)),
+                                             (lds_void *)(vals + i), 4, 0, 0);
+    }
+}
+
+// Store the first `count` positions of a sorted STRIDED tile of key/value
+// elements: each key with the value that its rank names among the staged
+// ones.  RANKS is a power of two above every rank: padding reads some LDS
+// word and is not stored (see store_bounded).
+template <uint32_t RANKS, class Src>
+__device__ __forceinline__ void store_elems(const Lines<true> &t, uint32_t *kdst, uint32_t *vdst, uint32_t count,
+                                            const uint32_t *vals, uint32_t lane, const Src &src)
+{
+    constexpr int B = 16;  // LDS reads in flight
+    const __amdgpu_buffer_rsrc_t ks = __builtin_amdgcn_make_buffer_rsrc(kdst, (short)0, (int)(count * 4u), 0x00020000);
+    const __amdgpu_buffer_rsrc_t vs = __builtin_amdgcn_make_buffer_rsrc(vdst, (short)0, (int)(count * 4u), 0x00020000);
+#pragma unroll
+    for (int r0 = 0; r0 < kLine; r0 += B) {
+        if ((uint32_t)(kWave * r0) >= count)
+            break;  // wave-uniform
+        uint32_t v[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+            v[i] = vals[elem_rank(t.e[r0 + i]) & (RANKS - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            uint32_t k = elem_key(t.e[r0 + i]);
+            if constexpr (Src::kMapped)
+                k = map_key(k, src.out_map.sign, src.out_map.rest, src.out_map.inverse);
+            const uint32_t off = opaque(4u * (kWave * (r0 + i) + lane));
+            __builtin_amdgcn_raw_buffer_store_b32(k, ks, (int)off, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b32(v[i], vs, (int)off, 0, 0);
+        }
+    }
 }
 
 // ----------------------------------------------------------- block sort body
@@ -722,22 +764,30 @@ template <bool P, bool SHEAR, class Src>
 __device__ __forceinline__ void wave_tile(Lines<P> &a, const SortItem &it, const Src &src, uint32_t t, uint32_t *lds,
                                           uint32_t lane)
 {
-    map_tile_in<P>(a, src);
+    if constexpr (!P)
+        map_tile_in<P>(a, src);
     if constexpr (SHEAR)
         shear_sort_blocked<P>(a, lds, lane);
-    else
-        sort_tile_blocked<P>(a, lds, lane);
+    else if (uniform(it.count) != 0)  // always; a block of its own, which the load's registers do not reach into
+        sort_tile_pairs(a, lds, lane);
     write_samples<P>(a, src.out_smp, src.pos(t), it.count, lane);
     to_strided(a, lds, lane);
-    if constexpr (P)
-        permute_values_lds(a, it.vs, it.count, lds, 0, it.count, lane, wave_lds_fence);
-    map_tile_out<P>(a, src);
-    store_tile<P>(a, it.kd, it.vd, it.count, lane);
+    if constexpr (P) {
+        const uint32_t count = uniform(it.count);
+        stage_values(uniform(it.vs), count, lds, lane);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        wave_lds_fence();
+        store_elems<kTile>(a, uniform(it.kd), uniform(it.vd), count, lds, lane, src);
+        wave_lds_fence();
+    } else {
+        map_tile_out<P>(a, src);
+        store_tile<P>(a, it.kd, it.vd, it.count, lane);
+    }
 }
 
 // Wave tiles of key/value sorts, and of keys under the ShearSort ablation.
 template <bool P, class Src, bool SHEAR = false>
-__global__ __launch_bounds__(kWave *kWavesPerGroup) void k_block_sort(Src src)
+__global__ __launch_bounds__(kWave *kWavesPerGroup) __attribute__((amdgpu_waves_per_eu(SHEAR ? 1 : 2))) void k_block_sort(Src src)
 {
     static_assert(P || SHEAR, "u32 keys take k_block_sort_keys");
     src.resolve();
@@ -750,7 +800,10 @@ __global__ __launch_bounds__(kWave *kWavesPerGroup) void k_block_sort(Src src)
         const uint32_t ln = opaque(lane);
         const SortItem it = src.get(t);
         Lines<P> a;
-        load_tile<P>(a, it.ks, it.count, ln, 0, pad_key(src));
+        if constexpr (P)
+            load_elems(a, uniform(it.ks), uniform(it.count), ln, 0, src);
+        else
+            load_tile<P>(a, it.ks, it.count, ln, 0, pad_key(src));
         wave_tile<P, SHEAR>(a, it, src, t, lds, ln);
     }
 }
@@ -773,7 +826,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void
         Lines<false> a;
         load_bounded(a, uniform(it.ks), count, lane, pad_key(src));
         map_tile_in<false>(a, src);
-        sort_tile_keys(a, lds, lane);
+        if (count != 0)  // always; a block of its own, which the load's registers do not reach into
+            sort_tile_keys(a, lds, lane);
         write_samples<false>(a, src.out_smp, src.pos(t), count, lane);
         to_strided_half(a, lds, lane);
         map_tile_out<false>(a, src);
@@ -839,8 +893,15 @@ struct TableGroupSrc {
 };
 
 // Key/value group tiles, persistent (block b handles groups b, b + grid, ...).
+// Bound by VALU instructions and the transposes of both element halves; at one
+// wave per SIMD (364 registers) neither overlapped the other's waits.  Loads
+// and stores through range-checked buffer resources and conversions one
+// register at a time fit 256 registers, so two groups share a CU; rounds 1..3
+// of the tiles stay out of the LDS.  Sub-tiles and rounds that a ragged group
+// holds only padding for are left out.  Measured: 2^26 pairs 2567 -> 2200 us (of
+// which the kernel 900 before), 1500 segments of up to 2^16 pairs 385 -> 285.
 template <int NW, class Src>
-__global__ __launch_bounds__(kWave *NW) void k_block_sort_group_pairs(Src src)
+__global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(2))) void k_block_sort_group_pairs(Src src)
 {
     src.resolve();
     __shared__ __align__(16) uint32_t lds[NW * kLdsWords];
@@ -850,23 +911,32 @@ __global__ __launch_bounds__(kWave *NW) void k_block_sort_group_pairs(Src src)
     for (uint32_t g = blockIdx.x; g < src.ngroups; g += gridDim.x) {
         const uint32_t ln = opaque(lane);
         const SortItem it = src.get(g, wave);
+        const uint32_t count = uniform(it.count), total = uniform(src.group_count(g));
+        const uint32_t *const vals = uniform(it.vs);
+        uint32_t *const kdst = uniform(it.kd), *const vdst = uniform(it.vd);
         Lines<true> t;
-        load_tile<true>(t, it.ks, it.count, ln, wave * kTile, pad_key(src));
-        map_tile_in<true>(t, src);
-        flip(t, wave);  // odd sub-tiles descending
-        sort_tile_blocked<true>(t, own, ln);
-        flip(t, wave);
-        group_rounds<NW, 7>(t, lds, ln, wave);
-        write_samples<true>(t, src.out_smp, src.pos(g, wave), it.count, ln);
+        load_elems(t, uniform(it.ks), count, ln, wave * kTile, src);
+        if (count != 0) {   // else padding only
+            flip(t, wave);  // odd sub-tiles descending
+            sort_tile_pairs(t, own, ln);
+            flip(t, wave);
+        }
+        // the rounds the group needs: later ones would merge with padding only
+        static_assert(NW == 4, "two group rounds");
+        if (total > kTile)
+            group_round<NW, 7>(t, lds, ln, wave);
+        if (total > 2 * kTile)
+            group_round<NW, 8>(t, lds, ln, wave);
+        write_samples<true>(t, src.out_smp, src.pos(g, wave), count, ln);
         to_strided(t, own, ln);
-        // group ranks are 4096 * wave + position; wave w stages the values of
-        // its own sub-tile, the LDS is shared by all waves of the group
-        const SortItem i0 = src.get(g, 0);
+        // group ranks are 4096 * wave + position; every wave stages the values
+        // of its own sub-tile, the LDS is shared by all waves of the group
         __syncthreads();
-        permute_values_lds(t, i0.vs, src.group_count(g), lds, kTile * wave, it.count, ln,
-                           [] { __syncthreads(); });
-        map_tile_out<true>(t, src);
-        store_tile<true>(t, it.kd, it.vd, it.count, ln);
+        stage_values(vals, count, lds + kTile * wave, ln);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        store_elems<NW * kTile>(t, kdst, vdst, count, lds, ln, src);
+        __syncthreads();
     }
 }
 
@@ -894,8 +964,9 @@ __global__ __launch_bounds__(kWave *kKeyGroupWaves) __attribute__((amdgpu_waves_
         Lines<false> t;
         load_bounded(t, uniform(it.ks), count, lane, pad_key(src));
         map_tile_in<false>(t, src);
-        sort_tile_keys(t, own, lane);
-        group_rounds_keys(t, lds, lane, wave);
+        if (count != 0)  // else padding only
+            sort_tile_keys(t, own, lane);
+        group_rounds_keys(t, lds, lane, wave, uniform(src.group_count(g)));
         write_samples<false>(t, src.out_smp, src.pos(g, wave), count, lane);
         to_strided_half(t, own, lane);
         map_tile_out<false>(t, src);
@@ -2459,8 +2530,7 @@ static hipError_t launch_group_src(const Src &src, hipStream_t s)
     if (src.ngroups == 0)
         return hipSuccess;
     if constexpr (P) {
-        // one wave per SIMD; persistent over the groups
-        const uint32_t groups = src.ngroups < cu_count() ? src.ngroups : cu_count();
+        const uint32_t groups = resident_blocks(k_block_sort_group_pairs<NW, Src>, kWave * NW, src.ngroups);
         hipLaunchKernelGGL((k_block_sort_group_pairs<NW, Src>), dim3(groups), dim3(kWave * NW), 0, s, src);
     } else {
         static_assert(NW == kKeyGroupWaves, "waves of a key group");
