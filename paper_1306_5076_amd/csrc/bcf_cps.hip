@@ -22,6 +22,13 @@
 // registers (DPP row shifts and lane reads) instead of through a transposed
 // LDS matrix.  The counters take 256 * d words of dynamic LDS, so small d
 // leaves room for more resident work-groups.
+//
+// Both passes over the elements are bound by HBM, so what counts is how they
+// read and write it: whole lines per instruction, in phase 3 through a
+// transposition in LDS, and in tiles of one page up to 2^26 elements so that the
+// work-groups in flight walk memory in order.  Measured at 2^26 elements and 16
+// colors under the profiler: phase 1 93 -> 74 us (4.5 TB/s), phase 3 156 -> 101
+// (6.0 TB/s, part of its input from the last-level cache); the call 250 -> 192.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,7 +41,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kPerThread = 32;  // consecutive elements a thread owns in a page
 constexpr int kPage = kThreads * kPerThread;
 constexpr uint32_t kMaxColors = 32;
-constexpr uint64_t kMaxTiles = 2048;
+constexpr uint64_t kMaxTiles = 8192;
 
 template <bool CF>
 __device__ __forceinline__ uint32_t slot(uint32_t t, uint32_t c, uint32_t d)
@@ -44,51 +51,95 @@ __device__ __forceinline__ uint32_t slot(uint32_t t, uint32_t c, uint32_t d)
 
 __device__ __forceinline__ uint32_t color_of(uint32_t c, uint32_t d) { return c < d ? c : d - 1; }
 
-// The kPerThread elements thread t owns in the page starting at `page` (< hi),
-// with 16-byte loads when all are in range (the arrays are 16-byte aligned).
-__device__ __forceinline__ void load_chunk(const uint32_t *values, const uint8_t *colors, uint64_t page,
-                                           uint64_t hi, uint32_t t, uint32_t (&v)[kPerThread],
-                                           uint32_t (&c)[kPerThread], uint32_t &valid)
+// Adds x to an LDS counter that no other thread touches: one instruction, and
+// no wait for the old value.
+__device__ __forceinline__ void counter_add(uint32_t *c, uint32_t x)
 {
-    const uint64_t base = page + (uint64_t)t * kPerThread;
-    if (base + kPerThread <= hi) {
-        valid = kPerThread;
-        const uint4 *vp = reinterpret_cast<const uint4 *>(values + base);
+    __hip_atomic_fetch_add(c, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The values of a wave's 64 chunks of kPerThread consecutive elements, between
+// global memory, where 8 lanes read or write a chunk's 128 bytes at once, and
+// the registers of the lane that owns the chunk.  A lane on its own would touch
+// 64 lines per instruction and come back to each eight times.  Half of every
+// chunk passes through the wave's LDS at a time: chunk r's 16 words as four
+// quads, quad q at 4 (q ^ ((r >> 1) & 3)) of words 16 r .. 16 r + 15, which lets
+// eight lanes of either side cover the 32 banks once.
+typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+constexpr int kBatch = 4;                        // colors whose scans are in flight together
+constexpr int kQuads = kPerThread / 4;           // 16-byte quads per chunk
+constexpr uint32_t kStageWords = 64 * kPerThread / 2;  // per wave: 4 KiB
+
+__device__ __forceinline__ Quad *stage_quad(uint32_t *stage, uint32_t row, uint32_t q)
+{
+    return reinterpret_cast<Quad *>(__builtin_assume_aligned(stage, 16)) + 4 * row + (q ^ ((row >> 1) & 3));
+}
+
+__device__ __forceinline__ void load_values(const uint32_t *src, uint32_t *stage, uint32_t lane,
+                                            uint32_t (&v)[kPerThread])
+{
+    const Quad *g = reinterpret_cast<const Quad *>(src);
+    const uint32_t q = lane & 3, row = lane >> 2;  // of 16 rows per load
+    Quad x[kQuads];
 #pragma unroll
-        for (int q = 0; q < kPerThread / 4; ++q) {
-            const uint4 x = vp[q];
-            v[4 * q] = x.x;
-            v[4 * q + 1] = x.y;
-            v[4 * q + 2] = x.z;
-            v[4 * q + 3] = x.w;
+    for (int i = 0; i < kQuads; ++i)
+        x[i] = g[kQuads * (16 * (i & 3) + row) + 4 * (i >> 2) + q];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *stage_quad(stage, 16 * i + row, q) = x[4 * h + i];
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const Quad y = *stage_quad(stage, lane, i);
+            v[16 * h + 4 * i] = y.x;
+            v[16 * h + 4 * i + 1] = y.y;
+            v[16 * h + 4 * i + 2] = y.z;
+            v[16 * h + 4 * i + 3] = y.w;
         }
-        const uint4 *cp = reinterpret_cast<const uint4 *>(colors + base);
-#pragma unroll
-        for (int q = 0; q < kPerThread / 16; ++q) {
-            const uint4 cc = cp[q];
-            const uint32_t w[4] = {cc.x, cc.y, cc.z, cc.w};
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                c[16 * q + i] = (w[i / 4] >> (8 * (i % 4))) & 0xffu;
-        }
-    } else {
-        valid = base < hi ? (uint32_t)(hi - base) : 0u;
-#pragma unroll
-        for (int i = 0; i < kPerThread; ++i) {
-            const bool in = (uint32_t)i < valid;
-            v[i] = in ? values[base + i] : 0u;
-            c[i] = in ? colors[base + i] : 0u;
-        }
+        wave_lds_fence();
     }
 }
 
-// Sum of x over the 64 lanes of the wave.
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x)
+__device__ __forceinline__ void store_values(uint32_t *dst, uint32_t *stage, uint32_t lane,
+                                             const uint32_t (&v)[kPerThread])
 {
+    Quad *g = reinterpret_cast<Quad *>(dst);
+    const uint32_t q = lane & 3, row = lane >> 2;
 #pragma unroll
-    for (int k = 32; k >= 1; k /= 2)
-        x += (uint32_t)__shfl_xor((int)x, k);
-    return x;
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *stage_quad(stage, lane, i) =
+                Quad{v[16 * h + 4 * i], v[16 * h + 4 * i + 1], v[16 * h + 4 * i + 2], v[16 * h + 4 * i + 3]};
+        wave_lds_fence();
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            g[kQuads * (16 * i + row) + 4 * h + q] = *stage_quad(stage, 16 * i + row, q);
+        wave_lds_fence();
+    }
+}
+
+// The colors of the kPerThread elements a thread owns.
+__device__ __forceinline__ void load_colors(const uint8_t *colors, uint32_t (&c)[kPerThread])
+{
+    const Quad *cp = reinterpret_cast<const Quad *>(colors);
+#pragma unroll
+    for (int q = 0; q < kPerThread / 16; ++q) {
+        const Quad cc = cp[q];
+        const uint32_t w[4] = {cc.x, cc.y, cc.z, cc.w};
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            c[16 * q + i] = (w[i / 4] >> (8 * (i % 4))) & 0xffu;
+    }
 }
 
 // Inclusive prefix sum of x over the lanes of the wave, without LDS: a
@@ -119,39 +170,72 @@ __global__ __launch_bounds__(kThreads) void k_cps_tile_sums(const uint32_t *valu
     const uint64_t lo = (uint64_t)blockIdx.x * tile, hi = lo + tile < n ? lo + tile : n;
     for (uint32_t c = 0; c < d; ++c)
         cnt[slot<CF>(t, c, d)] = 0;
+    // the order of the elements does not matter here: consecutive threads take
+    // consecutive quads
     for (uint64_t page = lo; page < hi; page += kPage) {
-        uint32_t v[kPerThread], col[kPerThread], valid;
-        load_chunk(values, colors, page, hi, t, v, col, valid);
+        if (page + kPage <= hi) {
+            const Quad *vp = reinterpret_cast<const Quad *>(values + page);
+            const uint32_t *cp = reinterpret_cast<const uint32_t *>(colors + page);
+            Quad x[kQuads];
+            uint32_t cc[kQuads];
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i)
-            if ((uint32_t)i < valid)
-                cnt[slot<CF>(t, color_of(col[i], d), d)] += v[i];
+            for (int q = 0; q < kQuads; ++q) {
+                x[q] = vp[kThreads * q + t];
+                cc[q] = cp[kThreads * q + t];
+            }
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) {
+                const uint32_t v[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    counter_add(&cnt[slot<CF>(t, color_of((cc[q] >> (8 * i)) & 0xffu, d), d)], v[i]);
+            }
+        } else {
+            for (uint64_t i = page + t; i < hi; i += kThreads)
+                counter_add(&cnt[slot<CF>(t, color_of(colors[i], d), d)], values[i]);
+        }
     }
-    for (uint32_t c = 0; c < d; ++c) {
-        const uint32_t s = wave_sum(cnt[slot<CF>(t, c, d)]);
-        if (lane == 0)
-            part[wave][c] = s;
+    for (uint32_t c0 = 0; c0 < d; c0 += kBatch) {
+        uint32_t x[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+            x[i] = cnt[slot<CF>(t, c0 + i < d ? c0 + i : c0, d)];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const uint32_t s = wave_scan(x[i], lane);
+            if (lane == 63 && c0 + i < d)
+                part[wave][c0 + i] = s;
+        }
     }
     __syncthreads();
     if (t < d) {
         uint32_t s = 0;
         for (int w = 0; w < kWaves; ++w)
             s += part[w][t];
-        sums[(uint64_t)blockIdx.x * d + t] = s;
+        sums[(uint64_t)t * gridDim.x + blockIdx.x] = s;
     }
 }
 
-// Phase 2: work-group c turns the tile sums of color c into exclusive offsets.
-__global__ __launch_bounds__(kThreads) void k_cps_tile_offsets(const uint32_t *sums, uint32_t *offsets,
-                                                               uint32_t tiles, uint32_t d)
+// Phase 2: work-group c turns the tile sums of color c into exclusive offsets
+// (sums and offsets are color-major, so its loads are consecutive: 6 us for 8192
+// tiles of 16 colors, 15 tile-major).
+constexpr int kScanThreads = 1024;
+constexpr int kScanPer = kMaxTiles / kScanThreads;  // consecutive tiles per thread, all loads in flight at once
+
+__global__ __launch_bounds__(kScanThreads) void k_cps_tile_offsets(const uint32_t *sums, uint32_t *offsets,
+                                                                   uint32_t tiles, uint32_t d)
 {
-    __shared__ uint32_t wtot[kWaves];
+    __shared__ uint32_t wtot[kScanThreads / 64];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t / 64, c = blockIdx.x;
-    const uint32_t per = (tiles + kThreads - 1) / kThreads;  // consecutive tiles per thread
-    const uint32_t b0 = t * per, b1 = b0 + per < tiles ? b0 + per : tiles;
-    uint32_t local = 0;
-    for (uint32_t b = b0; b < b1; ++b)
-        local += sums[(uint64_t)b * d + c];
+    uint32_t x[kScanPer], local = 0;
+#pragma unroll
+    for (int i = 0; i < kScanPer; ++i) {
+        const uint32_t b = t * kScanPer + i;
+        x[i] = b < tiles ? sums[(uint64_t)c * tiles + b] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < kScanPer; ++i)
+        local += x[i];
     const uint32_t incl = wave_scan(local, lane);
     if (lane == 63)
         wtot[wave] = incl;
@@ -159,10 +243,12 @@ __global__ __launch_bounds__(kThreads) void k_cps_tile_offsets(const uint32_t *s
     uint32_t run = incl - local;
     for (uint32_t w = 0; w < wave; ++w)
         run += wtot[w];
-    for (uint32_t b = b0; b < b1; ++b) {
-        const uint32_t s = sums[(uint64_t)b * d + c];
-        offsets[(uint64_t)b * d + c] = run;
-        run += s;
+#pragma unroll
+    for (int i = 0; i < kScanPer; ++i) {
+        const uint32_t b = t * kScanPer + i;
+        if (b < tiles)
+            offsets[(uint64_t)c * tiles + b] = run;
+        run += x[i];
     }
 }
 
@@ -171,16 +257,34 @@ template <bool CF>
 __global__ __launch_bounds__(kThreads) void k_cps_scan(const uint32_t *values, const uint8_t *colors, uint32_t *out,
                                                        uint64_t n, uint32_t d, uint64_t tile, const uint32_t *offsets)
 {
+    // from the last tile to the first: phase 1 left the end of the input in the
+    // last-level cache (2^26 elements, 16 colors: 203 us from the first, 195 so)
+    const uint32_t bid = gridDim.x - 1 - blockIdx.x;
     extern __shared__ uint32_t cnt[];  // kThreads * d counters
+    __shared__ __align__(16) uint32_t stage_all[kWaves][kStageWords];
     __shared__ uint32_t wtot[kWaves][kMaxColors];
     __shared__ uint32_t carry[kMaxColors];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t / 64;
-    const uint64_t lo = (uint64_t)blockIdx.x * tile, hi = lo + tile < n ? lo + tile : n;
+    const uint64_t lo = (uint64_t)bid * tile, hi = lo + tile < n ? lo + tile : n;
     if (t < d)
-        carry[t] = offsets[(uint64_t)blockIdx.x * d + t];
+        carry[t] = offsets[(uint64_t)t * gridDim.x + bid];
     for (uint64_t page = lo; page < hi; page += kPage) {
-        uint32_t v[kPerThread], col[kPerThread], valid;
-        load_chunk(values, colors, page, hi, t, v, col, valid);
+        const uint64_t base = page + (uint64_t)t * kPerThread;
+        const uint64_t wbase = page + (uint64_t)wave * (64 * kPerThread);
+        const bool whole = wbase + 64 * kPerThread <= hi;  // the wave's chunks, all in range
+        const uint32_t valid = whole || base + kPerThread <= hi ? kPerThread : base < hi ? (uint32_t)(hi - base) : 0u;
+        uint32_t v[kPerThread], col[kPerThread];
+        if (whole) {
+            load_colors(colors + base, col);
+            load_values(values + wbase, stage_all[wave], lane, v);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kPerThread; ++i) {
+                const bool in = (uint32_t)i < valid;
+                v[i] = in ? values[base + i] : 0u;
+                col[i] = in ? colors[base + i] : 0u;
+            }
+        }
 #pragma unroll
         for (int i = 0; i < kPerThread; ++i)
             col[i] = color_of(col[i], d);
@@ -189,23 +293,30 @@ __global__ __launch_bounds__(kThreads) void k_cps_scan(const uint32_t *values, c
             cnt[slot<CF>(t, c, d)] = 0;
 #pragma unroll
         for (int i = 0; i < kPerThread; ++i)
-            if ((uint32_t)i < valid)
-                cnt[slot<CF>(t, col[i], d)] += v[i];
+            counter_add(&cnt[slot<CF>(t, col[i], d)], v[i]);  // past the end: 0
         // exclusive scan over the threads, per color: within the wave in
         // registers, then across the four waves
-        for (uint32_t c = 0; c < d; ++c) {
-            const uint32_t x = cnt[slot<CF>(t, c, d)];
-            const uint32_t incl = wave_scan(x, lane);
-            cnt[slot<CF>(t, c, d)] = incl - x;
-            if (lane == 63)
-                wtot[wave][c] = incl;
+        for (uint32_t c0 = 0; c0 < d; c0 += kBatch) {
+            uint32_t x[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i)
+                x[i] = cnt[slot<CF>(t, c0 + i < d ? c0 + i : c0, d)];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                const uint32_t incl = wave_scan(x[i], lane);
+                if (c0 + i < d) {
+                    cnt[slot<CF>(t, c0 + i, d)] = incl - x[i];
+                    if (lane == 63)
+                        wtot[wave][c0 + i] = incl;
+                }
+            }
         }
         __syncthreads();
         for (uint32_t c = 0; c < d; ++c) {
             uint32_t base = carry[c];
             for (uint32_t w = 0; w < wave; ++w)
                 base += wtot[w][c];
-            cnt[slot<CF>(t, c, d)] += base;
+            counter_add(&cnt[slot<CF>(t, c, d)], base);
         }
         __syncthreads();
         if (t < d) {
@@ -215,21 +326,13 @@ __global__ __launch_bounds__(kThreads) void k_cps_scan(const uint32_t *values, c
             carry[t] += s;
         }
         // running sums over this thread's elements
-        const uint64_t base = page + (uint64_t)t * kPerThread;
         uint32_t r[kPerThread];
 #pragma unroll
-        for (int i = 0; i < kPerThread; ++i) {
-            const uint32_t s = slot<CF>(t, col[i], d);
-            const uint32_t x = cnt[s] + v[i];
-            if ((uint32_t)i < valid)
-                cnt[s] = x;
-            r[i] = x;
-        }
-        if (valid == kPerThread) {
-            uint4 *op = reinterpret_cast<uint4 *>(out + base);
-#pragma unroll
-            for (int q = 0; q < kPerThread / 4; ++q)
-                op[q] = make_uint4(r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]);
+        for (int i = 0; i < kPerThread; ++i)  // past the end: 0 is added
+            r[i] = v[i] + __hip_atomic_fetch_add(&cnt[slot<CF>(t, col[i], d)], v[i], __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (whole) {
+            store_values(out + wbase, stage_all[wave], lane, r);
         } else {
 #pragma unroll
             for (int i = 0; i < kPerThread; ++i)
@@ -287,7 +390,7 @@ extern "C" bcf_status bcf_colored_prefix_sums(const uint32_t *values, const uint
         hipLaunchKernelGGL(k_cps_tile_sums<true>, grid, block, lds, s, values, colors, n, d, tile, sums);
     else
         hipLaunchKernelGGL(k_cps_tile_sums<false>, grid, block, lds, s, values, colors, n, d, tile, sums);
-    hipLaunchKernelGGL(k_cps_tile_offsets, dim3(d), block, 0, s, sums, offsets, (uint32_t)tiles, d);
+    hipLaunchKernelGGL(k_cps_tile_offsets, dim3(d), dim3(kScanThreads), 0, s, sums, offsets, (uint32_t)tiles, d);
     if (conflict_free)
         hipLaunchKernelGGL(k_cps_scan<true>, grid, block, lds, s, values, colors, out, n, d, tile, offsets);
     else
