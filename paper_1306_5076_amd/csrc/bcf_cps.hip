@@ -25,10 +25,9 @@
 //
 // Both passes over the elements are bound by HBM, so what counts is how they
 // read and write it: whole lines per instruction, in phase 3 through a
-// transposition in LDS, and in tiles of one page up to 2^26 elements so that the
-// work-groups in flight walk memory in order.  Measured at 2^26 elements and 16
-// colors under the profiler: phase 1 93 -> 74 us (4.5 TB/s), phase 3 156 -> 101
-// (6.0 TB/s, part of its input from the last-level cache); the call 250 -> 192.
+// transposition in LDS.  Measured at 2^26 elements and 16 colors: 250 us with
+// every lane on its own 128 bytes, 203 so (one page per tile, 8192 tiles: 192, but
+// the temp size is that of at most 2048 tiles).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -41,7 +40,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kPerThread = 32;  // consecutive elements a thread owns in a page
 constexpr int kPage = kThreads * kPerThread;
 constexpr uint32_t kMaxColors = 32;
-constexpr uint64_t kMaxTiles = 8192;
+constexpr uint64_t kMaxTiles = 2048;
 
 template <bool CF>
 __device__ __forceinline__ uint32_t slot(uint32_t t, uint32_t c, uint32_t d)
@@ -217,7 +216,7 @@ __global__ __launch_bounds__(kThreads) void k_cps_tile_sums(const uint32_t *valu
 }
 
 // Phase 2: work-group c turns the tile sums of color c into exclusive offsets
-// (sums and offsets are color-major, so its loads are consecutive: 6 us for 8192
+// (sums and offsets are color-major, so its loads are consecutive: 9 us for 8192
 // tiles of 16 colors, 15 tile-major).
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = kMaxTiles / kScanThreads;  // consecutive tiles per thread, all loads in flight at once
@@ -258,7 +257,7 @@ __global__ __launch_bounds__(kThreads) void k_cps_scan(const uint32_t *values, c
                                                        uint64_t n, uint32_t d, uint64_t tile, const uint32_t *offsets)
 {
     // from the last tile to the first: phase 1 left the end of the input in the
-    // last-level cache (2^26 elements, 16 colors: 203 us from the first, 195 so)
+    // last-level cache (8 us of the call at 2^26 elements and 16 colors)
     const uint32_t bid = gridDim.x - 1 - blockIdx.x;
     extern __shared__ uint32_t cnt[];  // kThreads * d counters
     __shared__ __align__(16) uint32_t stage_all[kWaves][kStageWords];

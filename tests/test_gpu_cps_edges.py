@@ -1,5 +1,5 @@
-"""Colored prefix sums at the edges of a wave's 2048 elements and of the 8192
-tiles a call is cut into, bit-exact against the oracle, with the output in
+"""Colored prefix sums at the edges of a wave's 2048 elements and of tiles of
+several pages, bit-exact against the oracle, with the output in
 place and apart."""
 
 import numpy as np
