@@ -163,6 +163,15 @@ bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, cons
                           uint32_t k, uint32_t *keys_out, uint32_t *vals_out, void *temp,
                           uint64_t *temp_bytes, void *stream);
 
+/*
+ * Temp size of bcf_merge_runs for k runs, and of bcf_segmented_sort (pairs = 0)
+ * or bcf_segmented_sort_pairs (pairs != 0) for nseg segments, of at most n keys
+ * in all: what their query returns for offsets that end at n, without reading
+ * the device.  BCF_ERR_INVALID for n above 2^32 - 1.
+ */
+bcf_status bcf_merge_runs_temp(uint64_t n, uint32_t k, int pairs, uint64_t *temp_bytes);
+bcf_status bcf_segmented_sort_temp(uint64_t n, uint32_t nseg, int pairs, uint64_t *temp_bytes);
+
 /* bcf_merge_runs with HOST offsets, planned on the host (the plan goes to the
  * device with one copy through pinned staging); empty runs are dropped from
  * the plan.  The temp size depends on the offsets, not only on their total. */
@@ -175,8 +184,7 @@ bcf_status bcf_merge_runs_host(const uint32_t *keys_in, const uint32_t *vals_in,
  * independently (segments of up to 4096 keys in one wave tile, longer ones
  * block-sorted and then merged within the segment; all segments in one
  * block-sort launch per tile kind and one set of launches per merge level).
- * A segment's runs are merged four at a time while more than two remain
- * (bcf_tuning.merge_fan_in), then pairwise.
+ * A segment's runs are merged four at a time (bcf_tuning.merge_fan_in).
  *   seg_offsets  DEVICE, nseg+1 entries (u64)
  * Planned on the device, with the temp and capacity conventions of
  * bcf_merge_runs: the temp size does not depend on the tuning.
@@ -373,15 +381,12 @@ typedef struct {
                                   partition launch first */
     int32_t merge_fan_in;      /* runs merged per group by a merge pass of the sorts
                                   (bcf_sort_u32, bcf_sort_pairs_u32 and the int32 / float
-                                  forms) and of the segmented sorts (device- or host-planned,
-                                  keys or pairs).  0 (default): 4 for key/value sorts, for sorts
-                                  of at least 2^24 keys and for segmented sorts of at least
-                                  2^25 keys in total, else 2.  4 or 2: that fan-in at every
-                                  size.  A segment takes four-way steps while more than two
-                                  of its runs remain, then a binary one.  Four-way passes of the sorts need
-                                  sampled_partition (else 2 is used).  bcf_merge_runs and the
-                                  bucket merge of bcf_sort_u32_pb take four-way steps under 4,
-                                  and under 0 when a merge (a bucket) has at least 16 runs */
+                                  forms), of the segmented sorts (device- or host-planned,
+                                  keys or pairs), of bcf_merge_runs and of the bucket merge of
+                                  bcf_sort_u32_pb.  0 (default): 2 for sorts of fewer than
+                                  2^24 keys, else 4.  4 or 2: that fan-in at every size.
+                                  Four-way passes of the sorts need sampled_partition (else 2
+                                  is used) and end in a binary one where two runs remain */
 } bcf_tuning;
 
 void bcf_get_tuning(bcf_tuning *out);

@@ -426,7 +426,7 @@ void add_job4(MergePass &mp, uint64_t start, const uint64_t (&n)[4], uint32_t sr
     j.start = start;
     for (int r = 0; r < 4; ++r)
         j.n[r] = (uint32_t)n[r];
-    const uint32_t J = merge4_ab_segments(n[0] + n[1]), M = merge4_cd_cuts(n[2] + n[3]);
+    const uint32_t J = merge4_ab_segments(n[0] + n[1], n[2] + n[3]), M = merge4_cd_cuts(n[2] + n[3]);
     j.cut_off = mp.records4;
     j.item_off = mp.items4;
     j.task_off = mp.tasks4;
@@ -465,7 +465,7 @@ struct TableLayout {
     uint64_t block_off = 0, block_bytes = 0;    // single-wave tiles
     uint64_t group_off = 0, group_bytes = 0;    // multi-wave group tiles
     std::vector<uint64_t> jobs_off, map_off;
-    std::vector<uint64_t> jobs4_off, task_off, item_off, cuts4_off;  // fan-in 4 tables of each pass
+    std::vector<uint64_t> jobs4_off, item_off, cuts4_off;  // fan-in 4 tables of each pass
     uint64_t splits_off = 0;  // one u32 per tile of the largest pass (reused by every pass)
     uint64_t total = 0;
 };
@@ -489,8 +489,6 @@ TableLayout layout_tables(uint64_t base, size_t nblock, size_t ngroup, const std
         max_tiles = std::max(max_tiles, mp.tile_job.size());
         L.jobs4_off.push_back(o);
         o = align256(o + mp.jobs4.size() * sizeof(Merge4Job));
-        L.task_off.push_back(o);
-        o = align256(o + (uint64_t)mp.tasks4 * sizeof(uint32_t));
         L.item_off.push_back(o);
         o = align256(o + (uint64_t)mp.items4 * sizeof(uint32_t));
         L.cuts4_off.push_back(o);
@@ -562,17 +560,15 @@ bcf_status launch_tables(Bufs kb, Bufs vb, char *temp, const TablePlan &P, hipSt
     for (size_t p = 0; p < P.passes.size(); ++p) {
         const auto &mp = P.passes[p];
         if (!mp.jobs4.empty()) {
-            // the fan-in 4 merges of this pass (other segments than its binary
-            // jobs): maps, cut searches, merges
-            for (int phase = 0; phase < 3; ++phase) {
-                static const char *const names[2][3] = {{"map4_keys_table", "cuts4_keys_table", "merge4_keys_table"},
-                                                        {"map4_pairs_table", "cuts4_pairs_table", "merge4_pairs_table"}};
-                ProfScope ps(names[pairs][phase], s, phase == 2 ? 2.0 * eb * mp.keys4 : 0.0);
+            // the fan-in 4 merges of this pass: cut searches and map, merges
+            for (int phase = 0; phase < 2; ++phase) {
+                static const char *const names[2][2] = {{"cuts4_keys_table", "merge4_keys_table"},
+                                                        {"cuts4_pairs_table", "merge4_pairs_table"}};
+                ProfScope ps(names[pairs][phase], s, phase ? 2.0 * eb * mp.keys4 : 0.0);
                 BCF_TRY(dev_status(launch_merge4_table(
-                    kb, reinterpret_cast<const Merge4Job *>(temp + L.jobs4_off[p]), (uint32_t)mp.jobs4.size(),
-                    reinterpret_cast<uint32_t *>(temp + L.task_off[p]), mp.tasks4,
+                    kb, reinterpret_cast<const Merge4Job *>(temp + L.jobs4_off[p]), (uint32_t)mp.jobs4.size(), mp.tasks4,
                     reinterpret_cast<uint32_t *>(temp + L.item_off[p]), mp.items4, temp + L.cuts4_off[p], mp.keys4,
-                    phase, s, nullptr, pairs ? vb : Bufs{nullptr, nullptr, nullptr})));
+                    phase == 1, s, nullptr, pairs ? vb : Bufs{nullptr, nullptr, nullptr})));
             }
         }
         if (mp.tile_job.empty())
@@ -631,26 +627,17 @@ uint64_t plan_fingerprint(const uint64_t *off, uint32_t nseg, bool pairs)
 // never cross its boundaries, then merged pairwise until one run remains.
 // X_j(s), the buffer holding segment s after its pass j, alternates so that
 // its last pass lands in the output.
-// Merge steps of a segment of `runs` sorted runs: fan-in 4 while more than
-// two runs remain (when `four`), then binary steps until one run is left.
+// Merge steps of a segment of `runs` sorted runs until one is left: fan-in 4
+// (when `four`; jobs of two runs among them) or binary.
 std::vector<uint8_t> seg_fan_ins(uint64_t runs, bool four)
 {
     std::vector<uint8_t> fi;
     while (runs > 1) {
-        const uint8_t k = (four && runs > 2) ? 4 : 2;
+        const uint8_t k = four ? 4 : 2;
         fi.push_back(k);
         runs = (runs + k - 1) / k;
     }
     return fi;
-}
-
-// Whether the merges of a segmented sort of n keys (or pairs) use fan-in 4
-// steps under the tuning knob merge_fan_in (0: from 2^25 keys, where a pass
-// streams more than the last-level cache holds).
-bool seg_four_way(bool pairs, uint64_t n, int fan_in_knob)
-{
-    (void)pairs;
-    return fan_in_knob == 4 || (fan_in_knob == 0 && n >= kAutoFourWayMinN);
 }
 
 bcf_status plan_segmented(const uint64_t *off, uint32_t nseg, bool pairs, uint64_t gmin_knob, int fan_in_knob,
@@ -660,7 +647,7 @@ bcf_status plan_segmented(const uint64_t *off, uint32_t nseg, bool pairs, uint64
     const uint64_t n = off[nseg];
     const uint64_t gmin = group_min_keys(pairs, gmin_knob);
     const uint64_t grun = group_run_keys(pairs);
-    const bool four = seg_four_way(pairs, n, fan_in_knob);
+    const bool four = fan_in_knob != 2;  // fan-in 4 steps unless the tuning asks for binary ones
     std::vector<uint32_t> ps(nseg, 0);
     std::vector<uint64_t> run0(nseg, kTile);
     std::vector<std::vector<uint8_t>> fan(nseg);

@@ -140,12 +140,11 @@ hipError_t launch_block_sort_group_table(bool pairs, Bufs kb, Bufs vb, const Blo
 hipError_t launch_merge_table(bool pairs, Bufs kb, Bufs vb, const MergeJob *jobs,
                               const uint32_t *tile_job, uint32_t ntiles, uint32_t *splits,
                               bool partition, hipStream_t s, const uint32_t *count_dev = nullptr);
-// Fan-in 4 table pass (keys): AB / CD segment and cut counts of a job (the
-// planner sizes its records and items by them), and the three launches of a
-// pass over `njobs` jobs (phase 0: the maps from cut searches and item slots
-// to jobs, task_job and item_job, from the jobs' first indices; 1: the
-// `tasks` cut searches, which also write every job's first and last AB cut
-// into `cuts`; 2: the merges of the `items` slots).  `keys` is the number of
+// Fan-in 4 table pass: AB / CD segment and cut counts of a job (the planner
+// sizes its records and items by them), and the two launches of a pass over
+// `njobs` jobs (merge = false: the `tasks` cut searches, which also write every
+// job's first and last AB cut into `cuts`, and the map item_job from item slots
+// to jobs; true: the merges of the `items` slots).  `keys` is the number of
 // keys the pass merges (it decides the nontemporal hints).
 // Cut steps of the four-way merge (multiples of the 64-key sample blocks, at
 // most half a 4096-key tile): AB cuts every kAbStep keys, CD cuts every
@@ -159,7 +158,15 @@ __host__ __device__ constexpr uint32_t ab_segments(uint64_t nab)
     return nab > kAbStep ? (uint32_t)((nab + kAbStep - 1) / kAbStep) : 1u;
 }
 __host__ __device__ constexpr uint32_t cd_cuts(uint64_t ncd) { return ncd ? (uint32_t)((ncd - 1) / kCdStep) : 0u; }
-__host__ __device__ constexpr uint32_t merge4_ab_segments(uint64_t nab) { return ab_segments(nab); }
+// Table jobs whose CD side is empty (two runs, or one to copy) are cut every
+// kPairStep keys: their items have one or two pieces, which fill a whole tile.
+constexpr uint32_t kPairStep = 4096;
+__host__ __device__ constexpr uint32_t merge4_ab_step(uint64_t ncd) { return ncd ? kAbStep : kPairStep; }
+__host__ __device__ constexpr uint32_t merge4_ab_segments(uint64_t nab, uint64_t ncd)
+{
+    const uint32_t step = merge4_ab_step(ncd);
+    return nab > step ? (uint32_t)((nab + step - 1) / step) : 1u;
+}
 __host__ __device__ constexpr uint32_t merge4_cd_cuts(uint64_t ncd) { return cd_cuts(ncd); }
 // Cut searches, item slots and cut records of one fan-in 4 job (J AB
 // segments, M interior CD cuts): at least one search (the first writes the
@@ -172,16 +179,13 @@ __host__ __device__ constexpr uint32_t merge4_records(uint32_t J, uint32_t M) { 
 // launches then stride over the counts with grids sized by the chip.
 // With vb.in set the merges carry values (stable key/value jobs, values laid
 // out like the keys in vb's three buffers).
-hipError_t launch_merge4_table(Bufs kb, const Merge4Job *jobs, uint32_t njobs, uint32_t *task_job, uint32_t tasks,
-                               uint32_t *item_job, uint32_t items, void *cuts, uint64_t keys, int phase,
-                               hipStream_t s, const uint32_t *counts_dev = nullptr,
+hipError_t launch_merge4_table(Bufs kb, const Merge4Job *jobs, uint32_t njobs, uint32_t tasks, uint32_t *item_job,
+                               uint32_t items, void *cuts, uint64_t keys, bool merge, hipStream_t s,
+                               const uint32_t *counts_dev = nullptr,
                                Bufs vb = Bufs{nullptr, nullptr, nullptr});
 hipError_t launch_check_runs(const uint32_t *keys, const uint64_t *run_ends_dev, uint32_t k,
                              uint64_t n, uint32_t *flag, hipStream_t s);
 
-// Segmented sorts of at least this many keys in all take four-way merge
-// steps under the default (auto) fan-in.
-constexpr uint64_t kAutoFourWayMinN = 1ull << 25;
 // Sorts of keys take four-way merge passes under the default fan-in from
 // this many keys (uniform keys, binary / four-way: 2^18 0.072 / 0.076 ms,
 // 2^20 0.102 / 0.104, 2^22 0.168 / 0.156, 2^23 0.196 / 0.198, 2^24 0.365 /

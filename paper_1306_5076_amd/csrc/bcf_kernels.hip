@@ -23,6 +23,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
+#include <mutex>
+#include <utility>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -1394,6 +1398,7 @@ __global__ __launch_bounds__(kWave *merge_group_waves<MODE>()) void k_merge(Src 
 // no item.
 
 constexpr uint32_t kHalfTile = kTile / 2;
+static_assert(kPairStep == kTile, "items of two pieces");
 static_assert(kAbStep % kLine == 0 && kCdStep % kLine == 0 && kAbStep <= kHalfTile && kCdStep <= kHalfTile,
               "cut steps");
 
@@ -1664,7 +1669,7 @@ __device__ __forceinline__ void emit_blocked(Lines<false> &t, uint32_t *lds, uin
     store_bounded<NT>(t, kdst + gpos, count, lane);
 }
 
-// An item of one piece (count <= 2048 keys, already sorted) copied to array
+// At most 2048 keys of an item of one piece (already sorted) copied to array
 // position gpos with the samples that fall inside it, by coalesced loads and
 // stores: every lane moves the elements lane + 64 k.
 template <bool NT, bool MAP>
@@ -1828,7 +1833,7 @@ __device__ __forceinline__ void merge4_item(const Group4 &G, const uint4 &c0, co
 {
     const uint32_t pa = c1.x - c0.x, pb = c1.y - c0.y, pc = c1.z - c0.z, pd = c1.w - c0.w;
     const uint32_t sx = pa + pb, sy = pc + pd, count = sx + sy;
-    if (count == 0 || sx > kHalfTile || sy > kHalfTile)
+    if (count == 0 || sx > (sy == 0 ? (uint32_t)kTile : kHalfTile) || sy > kHalfTile)
         return;
     const uint64_t gpos = G.start + c0.x + c0.y + c0.z + c0.w;
     const uint32_t pieces = (pa != 0) + (pb != 0) + (pc != 0) + (pd != 0);
@@ -1836,7 +1841,10 @@ __device__ __forceinline__ void merge4_item(const Group4 &G, const uint4 &c0, co
     const uint32_t oa = c0.x, ob = ob0 + c0.y, oc = oc0 + c0.z, od = od0 + c0.w;
     if (pieces == 1) {
         // one piece: already sorted, copied as it is (no network, no LDS)
-        copy4<NT, MAP>(K + (pa ? oa : pb ? ob : pc ? oc : od), kdst, gpos, count, out_smp, km, lane);
+        const uint32_t *x = K + (pa ? oa : pb ? ob : pc ? oc : od);
+        copy4<NT, MAP>(x, kdst, gpos, min(count, kHalfTile), out_smp, km, lane);
+        if (count > kHalfTile)
+            copy4<NT, MAP>(x + kHalfTile, kdst, gpos + kHalfTile, count - kHalfTile, out_smp, km, lane);
         return;
     }
     HalfPieces hp;
@@ -1845,13 +1853,17 @@ __device__ __forceinline__ void merge4_item(const Group4 &G, const uint4 &c0, co
         // the upper half, complemented
         hp = HalfPieces{{oa, oc}, {pa, pc}, {ob + kHalfTile - 1, od + kHalfTile - 1}, {pb, pd}, ~0u};
     } else {
-        // the first nonempty piece X ascending at the front of the lower half,
-        // the second one Y (if any) reversed at the back of the upper half
+        // the first nonempty piece X ascending from the front of the tile, the
+        // second one Y reversed at its back; either may reach into the other half
         const uint32_t ox = pa ? oa : pb ? ob : pc ? oc : od;
         const uint32_t nx = pa ? pa : pb ? pb : pc ? pc : pd;
         const uint32_t oy = (pa && pb) ? ob : ((pa || pb) && pc) ? oc : od;
-        const uint32_t ny = pieces == 2 ? count - nx : 0;
-        hp = HalfPieces{{ox, 0}, {nx, 0}, {0, oy + kHalfTile - 1}, {0, ny}, 0u};
+        const uint32_t ny = count - nx;
+        hp = HalfPieces{{ox, ox + kHalfTile},
+                        {min(nx, kHalfTile), nx > kHalfTile ? nx - kHalfTile : 0},
+                        {oy + 2 * kHalfTile - 1, oy + kHalfTile - 1},
+                        {ny > kHalfTile ? ny - kHalfTile : 0, min(ny, kHalfTile)},
+                        0u};
     }
     Lines<false> t;
     load_item<false>(t, K, hp, lane);
@@ -1982,7 +1994,7 @@ __device__ __forceinline__ void merge4_item_pairs(const Group4 &G, const uint4 &
 {
     const uint32_t pa = c1.x - c0.x, pb = c1.y - c0.y, pc = c1.z - c0.z, pd = c1.w - c0.w;
     const uint32_t sx = pa + pb, sy = pc + pd, count = sx + sy;
-    if (count == 0 || sx > kHalfTile || sy > kHalfTile)
+    if (count == 0 || sx > (sy == 0 ? (uint32_t)kTile : kHalfTile) || sy > kHalfTile)
         return;
     const uint64_t gpos = G.start + c0.x + c0.y + c0.z + c0.w;
     const uint32_t pieces = (pa != 0) + (pb != 0) + (pc != 0) + (pd != 0);
@@ -1990,17 +2002,30 @@ __device__ __forceinline__ void merge4_item_pairs(const Group4 &G, const uint4 &
     if (pieces == 1) {
         const uint32_t o = pa ? oa : pb ? ob : pc ? oc : od;
         const SampleSet none{nullptr, nullptr, nullptr, nullptr};
-        copy4<NT, MAP>(K + o, kdst, gpos, count, out_smp, km, lane);
-        copy4<NT, false>(V + o, vdst, gpos, count, none, KeyMap{}, lane);
+        const uint32_t part = min(count, kHalfTile);
+        copy4<NT, MAP>(K + o, kdst, gpos, part, out_smp, km, lane);
+        copy4<NT, false>(V + o, vdst, gpos, part, none, KeyMap{}, lane);
+        if (count > kHalfTile) {
+            copy4<NT, MAP>(K + o + kHalfTile, kdst, gpos + kHalfTile, count - kHalfTile, out_smp, km, lane);
+            copy4<NT, false>(V + o + kHalfTile, vdst, gpos + kHalfTile, count - kHalfTile, none, KeyMap{}, lane);
+        }
         return;
     }
     // every item of two or more pieces takes the four-piece layout and both
     // networks (empty pieces are padding): one code path, which keeps the
     // kernel at 256 registers, two waves per SIMD (a separate two-piece path
     // without the first network spilled at that bound)
-    const HalfPieces hp{{oa, oc}, {pa, pc}, {ob + kHalfTile - 1, od + kHalfTile - 1}, {pb, pd}, ~0u};
+    // A and B on their own fill the whole tile, A ascending from its front and
+    // B reversed at its back: either half holds a bitonic sequence as before
+    constexpr uint32_t H = kHalfTile;
+    const bool two = sy == 0;
+    const HalfPieces hp{{oa, two ? oa + H : oc},
+                        {two ? min(pa, H) : pa, two ? (pa > H ? pa - H : 0) : pc},
+                        {ob + (two ? 2 * H : H) - 1, (two ? ob : od) + H - 1},
+                        {two ? (pb > H ? pb - H : 0) : pb, two ? min(pb, H) : pd},
+                        ~0u};
     const ItemRanks ir{{0, pa, pa + pb, pa + pb + pc}, {pa ? oa : ob, ob, oc, od}};
-    const uint32_t rf[2] = {0, pa + pb}, rb[2] = {pa, pa + pb + pc};
+    const uint32_t rf[2] = {0, two ? H : pa + pb}, rb[2] = {two ? pa + H : pa, two ? pa : pa + pb + pc};
     Lines<true> t;
     load_item_pairs(t, K, hp, rf, rb, lane);
     // both halves merged at once, back to STRIDED, the CD half complemented back
@@ -2097,7 +2122,7 @@ __global__ __launch_bounds__(kWave *kMerge4Waves) __attribute__((amdgpu_waves_pe
 struct Merge4Table {
     Bufs kb;
     const Merge4Job *jobs;
-    uint32_t *task_job, *item_job;
+    uint32_t *item_job;
     uint32_t njobs, tasks, items;  // bounds when counts is set
     uint4 *cuts;
     const uint32_t *counts;        // device words (jobs, searches, item slots), or nullptr
@@ -2126,62 +2151,43 @@ __device__ __forceinline__ Group4 group_of_job(const Merge4Job &j)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         G.n[r] = j.n[r];
-    G.J = ab_segments((uint64_t)j.n[0] + j.n[1]);
-    G.M = cd_cuts((uint64_t)j.n[2] + j.n[3]);
+    const uint64_t ncd = (uint64_t)j.n[2] + j.n[3];
+    G.J = merge4_ab_segments((uint64_t)j.n[0] + j.n[1], ncd);
+    G.M = cd_cuts(ncd);
     return G;
 }
 
-// The maps of a table pass: search t and item slot i to the job whose range
-// (task_off, item_off; ascending, every job has at least one of each) holds
-// them, by binary search over the job list.
-__global__ __launch_bounds__(256) void k_map4_table(Merge4Table src)
-{
-    src.resolve();
-    const uint32_t njobs = src.njobs;
-    auto owner = [&](uint32_t x, bool items) {
-        uint32_t lo = 0, hi = njobs;  // the job's first index <= x, in [lo, hi)
-        while (hi - lo > 1) {
-            const uint32_t mid = lo + (hi - lo) / 2;
-            if ((items ? src.jobs[mid].item_off : src.jobs[mid].task_off) <= x)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        return lo;
-    };
-    const uint32_t most = src.items > src.tasks ? src.items : src.tasks;
-    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < most; i += gridDim.x * 256) {
-        if (i < src.items)
-            src.item_job[i] = owner(i, true);
-        if (i < src.tasks)
-            src.task_job[i] = owner(i, false);
-    }
-}
-
 // Searches of a table pass read the keys themselves (no samples), so every
-// deep round fetches its own lines: four lanes per search (4-ary rounds on the
-// cut's side, binary counts in each run of the other) fetch fewer lines per
-// round and keep sixteen searches in flight per wave.  Measured over the
-// table passes of a 1.01e9-key segmented sort: 16 lanes 1.21 ms, 8 lanes
-// 0.94-0.97 ms, 4 lanes 0.86 ms.
-constexpr int kTableCutLanesLog = 2;
-constexpr uint32_t kTableCutLanes = 1u << kTableCutLanesLog;
-constexpr uint32_t kTableCutsPerWave = kWave / kTableCutLanes;
+// deep round fetches its own lines.  Many searches: four lanes each (4-ary
+// rounds on the cut's side, binary counts in each run of the other) fetch fewer
+// lines per round and keep sixteen searches in flight per wave.  Measured over
+// the table passes of a 1.01e9-key segmented sort: 16 lanes 1.21 ms, 8 lanes
+// 0.94-0.97 ms, 4 lanes 0.86 ms.  Few searches leave the chip empty and are bound
+// by their rounds: sixteen lanes each (up to kFewCuts searches, two waves per
+// SIMD).
+constexpr int kTableCutLanesLog = 2, kFewCutLanesLog = 4;
+constexpr uint32_t kFewCuts = 1u << 14;
 
-// Cut searches of a table pass, kTableCutsPerWave per wave: task t
+// Cut searches of a table pass, 2^LOG lanes each: task t
 // of its job is AB cut t + 1 (t < J - 1) or CD cut t + 2 - J; the job's task
 // 0 also writes its records P[0] and P[J] (a job with no cut to search has
 // one task for that alone).
+template <int LOG>
 __device__ __forceinline__ void cut4_table_task(const Merge4Table &src, uint32_t task, uint32_t lane, uint32_t part)
 {
+    constexpr uint32_t kLanes = 1u << LOG;
     const bool in_range = task < src.tasks;
-    const Merge4Job jb = src.jobs[src.task_job[in_range ? task : 0]];
+    // the job that holds the task: task_off ascends, every job has at least one
+    uint32_t next = 1, last = src.njobs;
+    search_level<1, LOG>(next, last, lane,
+                                       [&](uint32_t i) { return src.jobs[i].task_off > (in_range ? task : 0); });
+    const Merge4Job jb = src.jobs[next - 1];
     const Group4 G = group_of_job(jb);
     const uint32_t t = in_range ? task - jb.task_off : 0;
     const bool ab = t + 1 < G.J;
     const uint32_t idx = ab ? t + 1 : t + 2 - G.J;  // AB cut j or CD cut m
     const bool valid = in_range && (ab ? idx < G.J : (idx >= 1 && idx <= G.M));
-    if (in_range && t == 0 && (lane & (kTableCutLanes - 1)) == 0) {
+    if (in_range && t == 0 && (lane & (kLanes - 1)) == 0) {
         uint4 *P = src.cuts + jb.cut_off;
         P[0] = make_uint4(0, 0, 0, 0);
         P[G.J] = make_uint4(G.n[0], G.n[1], G.n[2], G.n[3]);
@@ -2191,27 +2197,27 @@ __device__ __forceinline__ void cut4_table_task(const Merge4Table &src, uint32_t
     const uint32_t *K = buf_in(src.kb, jb.src) + jb.start;
     const uint32_t n0 = ab ? G.n[0] : G.n[2], n1 = ab ? G.n[1] : G.n[3];
     const uint32_t *A = K + (ab ? 0u : G.n[0] + G.n[1]), *B = A + n0;
-    const uint32_t d = ab ? idx * kAbStep : idx * kCdStep;
+    const uint32_t d = idx * (ab ? merge4_ab_step((uint64_t)G.n[2] + G.n[3]) : kCdStep);
     uint32_t lo = d > n1 ? d - n1 : 0, hi = d < n0 ? d : n0;
     if (!valid)
         lo = hi = 0;
-    search_level<1, kTableCutLanesLog>(lo, hi, lane, [&](uint32_t i) { return A[i] > B[d - 1 - i]; });
+    search_level<1, LOG>(lo, hi, lane, [&](uint32_t i) { return A[i] > B[d - 1 - i]; });
     const uint32_t s0 = lo, s1 = d - s0;
     uint32_t k = 0;
     if (valid)
         k = (s0 < n0 && (s1 >= n1 || A[s0] <= B[s1])) ? A[s0] : B[s1];
     // the other side: the upper half of a search's lanes counts in its second
     // run.  An AB cut counts keys below k, a CD cut keys at most k.
-    const uint32_t second = (lane / (kTableCutLanes / 2)) & 1;
+    const uint32_t second = (lane / (kLanes / 2)) & 1;
     const uint32_t nr = !valid ? 0 : (ab ? (second ? G.n[3] : G.n[2]) : (second ? G.n[1] : G.n[0]));
     const uint32_t ro = ab ? G.n[0] + G.n[1] + (second ? G.n[2] : 0) : (second ? G.n[0] : 0);
     const uint32_t *R = K + ro;
     const bool strict = !ab;
     uint32_t rlo = 0, rhi = nr;
-    search_level<1, kTableCutLanesLog - 1>(rlo, rhi, lane, [&](uint32_t i) { return strict ? R[i] > k : R[i] >= k; });
-    const uint32_t first = lane & ~(kTableCutLanes - 1);
-    const uint32_t o0 = __shfl(rlo, first), o1 = __shfl(rlo, first + kTableCutLanes / 2);
-    if (!valid || (lane & (kTableCutLanes - 1)) != 0)
+    search_level<1, LOG - 1>(rlo, rhi, lane, [&](uint32_t i) { return strict ? R[i] > k : R[i] >= k; });
+    const uint32_t first = lane & ~(kLanes - 1);
+    const uint32_t o0 = __shfl(rlo, first), o1 = __shfl(rlo, first + kLanes / 2);
+    if (!valid || (lane & (kLanes - 1)) != 0)
         return;
     uint4 *P = src.cuts + jb.cut_off;
     if (ab)
@@ -2220,15 +2226,30 @@ __device__ __forceinline__ void cut4_table_task(const Merge4Table &src, uint32_t
         P[G.J + 1 + idx] = make_uint4(o0, o1, s0, s1);
 }
 
+template <int LOG>
 __global__ __launch_bounds__(256) void k_cuts4_table(Merge4Table src)
 {
+    constexpr uint32_t kLanes = 1u << LOG, kCuts = kWave / kLanes;  // searches per wave
     src.resolve();
     const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t part = lane / kTableCutLanes;
+    const uint32_t part = lane / kLanes;
     const uint32_t waves = gridDim.x * (256 / kWave);
+    // the map for the merges: item slot i to the job whose range (item_off;
+    // ascending, every job has at least one) holds it
+    for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < src.items; i += gridDim.x * 256) {
+        uint32_t lo = 0, hi = src.njobs;  // the job's first slot <= i, in [lo, hi)
+        while (hi - lo > 1) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            if (src.jobs[mid].item_off <= i)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        src.item_job[i] = lo;
+    }
     for (uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / kWave) + threadIdx.x / kWave);
-         kTableCutsPerWave * wave < src.tasks; wave += waves)
-        cut4_table_task(src, kTableCutsPerWave * wave + part, lane, part);
+         kCuts * wave < src.tasks; wave += waves)
+        cut4_table_task<LOG>(src, kCuts * wave + part, lane, part);
 }
 
 // One item slot of a table pass.
@@ -2712,40 +2733,43 @@ hipError_t launch_merge4_regular(const uint32_t *ksrc, uint32_t *kdst, uint64_t 
 template <class K>
 static uint32_t resident_blocks(K kernel, int threads, uint64_t need)
 {
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu <= 0)
-        per_cu = 1, cus = 256;
-    const uint64_t most = (uint64_t)cus * per_cu;
+    // the runtime is asked once per kernel and device: a plan of few keys has
+    // a dozen of these launches
+    static std::mutex mu;
+    static std::map<std::pair<const void *, int>, uint64_t> known;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess)
+        dev = 0;
+    const std::lock_guard<std::mutex> hold(mu);
+    uint64_t &most = known[{reinterpret_cast<const void *>(kernel), dev}];
+    if (most == 0) {
+        int cus = 0, per_cu = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu <= 0)
+            per_cu = 1, cus = 256;
+        most = (uint64_t)cus * per_cu;
+    }
     return (uint32_t)(need < most ? need : most);
 }
 
-hipError_t launch_merge4_table(Bufs kb, const Merge4Job *jobs, uint32_t njobs, uint32_t *task_job, uint32_t tasks,
-                               uint32_t *item_job, uint32_t items, void *cuts, uint64_t keys, int phase, hipStream_t s,
+hipError_t launch_merge4_table(Bufs kb, const Merge4Job *jobs, uint32_t njobs, uint32_t tasks, uint32_t *item_job,
+                               uint32_t items, void *cuts, uint64_t keys, bool merge, hipStream_t s,
                                const uint32_t *counts_dev, Bufs vb)
 {
-    Merge4Table src{kb, jobs, task_job, item_job, njobs, tasks, items, static_cast<uint4 *>(cuts), counts_dev, vb};
+    Merge4Table src{kb, jobs, item_job, njobs, tasks, items, static_cast<uint4 *>(cuts), counts_dev, vb};
     const bool pairs = vb.in != nullptr;
     if (njobs == 0)
         return hipSuccess;
     const bool dev_counts = counts_dev != nullptr;
-    if (phase == 0) {
-        const uint32_t most = tasks > items ? tasks : items;
-        const uint64_t need = (most + 255) / 256;
-        const uint32_t grid = dev_counts ? resident_blocks(k_map4_table, 256, need) : (uint32_t)need;
-        if (grid == 0)
-            return hipSuccess;
-        hipLaunchKernelGGL(k_map4_table, dim3(grid), dim3(256), 0, s, src);
-        return hipGetLastError();
-    }
-    if (phase == 1) {
+    if (!merge) {
         if (tasks == 0)
             return hipSuccess;
-        const uint32_t per_block = kTableCutsPerWave * (256 / kWave);
-        const uint64_t need = (tasks + per_block - 1) / per_block;
-        const uint32_t grid = dev_counts ? resident_blocks(k_cuts4_table, 256, need) : (uint32_t)need;
-        hipLaunchKernelGGL(k_cuts4_table, dim3(grid), dim3(256), 0, s, src);
+        const bool few = tasks <= kFewCuts;
+        const uint32_t per_block = 256u >> (few ? kFewCutLanesLog : kTableCutLanesLog);
+        const uint64_t need = ((uint64_t)tasks + per_block - 1) / per_block;
+        const auto kernel = few ? k_cuts4_table<kFewCutLanesLog> : k_cuts4_table<kTableCutLanesLog>;
+        const uint32_t grid = dev_counts ? resident_blocks(kernel, 256, need) : (uint32_t)need;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, src);
         return hipGetLastError();
     }
     if (items == 0)

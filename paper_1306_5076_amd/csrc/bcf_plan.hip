@@ -5,10 +5,14 @@
 // graph stays valid when the offsets change between replays (as long as the
 // total stays within the capacity the temp buffer was sized for).
 //
-// The merges are the paper's binary merging (Sec. 3.2) of groups of runs:
-// group g's runs are merged pairwise, pass after pass, until one run remains;
-// every group has its own pass count and buffer parity, so its last pass
-// writes the output.  Three kinds of groups:
+// The merges are the paper's merging (Sec. 3.2) of groups of runs: group g's
+// runs are merged four at a time (or pairwise, when the tuning asks for it), pass
+// after pass, until one run remains; every group has its own pass count and
+// buffer parity, so its last pass writes the output.  Calls on few keys are
+// bound by the launches, whose number only depends on what the host knows (the
+// capacity and the number of offsets): four planner launches, then two per
+// four-way level, which takes the jobs of two runs and the copies along.
+// Three kinds of groups:
 //   * merge_runs: one group of k explicit runs [off[r], off[r+1]);
 //   * buckets (the final merge after a distribution, Sec. 3.2 and 3.3): group
 //     b holds the s pieces [off[b s + r], off[b s + r + 1]) of bucket b; a
@@ -70,15 +74,14 @@ __host__ __device__ inline uint32_t ceil_log2_u(uint64_t x)
 
 enum GroupKind : uint32_t { kKindRuns = 0, kKindBuckets = 1, kKindSegments = 2 };
 
-// One group as the planner sees it.  A segment (keys, fan-in 4 on) first
-// takes `steps4` fan-in 4 steps while more than two runs remain, then its
-// binary steps.
+// One group as the planner sees it: `steps4` fan-in 4 steps, or `merges` binary
+// ones, until one run remains.
 struct GroupInfo {
     uint32_t first;   // explicit runs: index of the group's first offset
     uint32_t nruns;   // runs before the merge passes
-    uint32_t steps4;  // fan-in 4 steps (segments only)
-    uint32_t merges;  // binary merge passes after them
-    uint32_t passes;  // steps4 + merges, or merges + 1 with a final copy, or 1 copy
+    uint32_t steps4;  // fan-in 4 steps
+    uint32_t merges;  // binary steps (none under fan-in 4)
+    uint32_t passes;  // the steps, one more with a final copy, or 1 copy
     uint32_t run0;    // segments: run length after the block sort (0: explicit runs)
     uint64_t start, end;
 };
@@ -96,8 +99,8 @@ struct PlanArgs {
     uint64_t gmin;       // segments: group tiles from this many keys (and more than 4096)
     uint32_t grun;       // segments: keys per group tile
     uint32_t PM;         // merge passes planned
-    uint32_t four;       // segments: fan-in 4 steps 0 off, 1 on, 2 from kAutoFourWayMinN keys in all
-    uint32_t PM4;        // passes with fan-in 4 tables (at most kMaxPlan4Passes)
+    uint32_t four;       // fan-in 4 steps (PM4 passes, PM = 0) or binary ones (PM passes, PM4 = 0)
+    uint32_t PM4;        // at most kMaxPlan4Passes
     uint64_t cap;        // the most keys the temp buffer holds
     uint32_t *status;    // 0: plan valid; 1: offsets invalid or past the capacity
     // block-sort tiles (segments): counts per group, prefix, lists, totals
@@ -135,12 +138,11 @@ __device__ GroupInfo group_info(const PlanArgs &a, uint32_t g)
         gi.nruns = (uint32_t)((len + gi.run0 - 1) / gi.run0);
         uint32_t r = gi.nruns;
         gi.steps4 = 0;
-        const bool four = a.four == 1 || (a.four == 2 && a.off[a.G] >= kAutoFourWayMinN);
-        while (four && r > 2 && gi.steps4 < a.PM4) {
+        while (a.four && r > 1 && gi.steps4 < a.PM4) {
             r = (r + 3) / 4;
             ++gi.steps4;
         }
-        gi.merges = ceil_log2_u(r);
+        gi.merges = a.four ? 0 : ceil_log2_u(r);
         gi.passes = gi.steps4 + gi.merges;
         gi.first = 0;
     } else {
@@ -154,14 +156,12 @@ __device__ GroupInfo group_info(const PlanArgs &a, uint32_t g)
             gi.nruns = a.s;
         }
         const bool pivot = a.kind == kKindBuckets && a.pivot && (g & 1u);
-        // explicit runs: fan-in 4 steps only when the host asked for them (it
-        // plans the pass count, and the extra copy of an in-place merge, the same way)
         uint32_t r = gi.nruns;
-        while (a.four == 1 && !pivot && r > 2 && gi.steps4 < a.PM4) {
+        while (a.four && !pivot && r > 1 && gi.steps4 < a.PM4) {
             r = (r + 3) / 4;
             ++gi.steps4;
         }
-        gi.merges = pivot ? 0 : ceil_log2_u(r);
+        gi.merges = pivot || a.four ? 0 : ceil_log2_u(r);
         const uint32_t levels = gi.steps4 + gi.merges;
         if (a.kind == kKindRuns)
             gi.passes = levels + (a.extra_copy ? 1 : 0);
@@ -183,18 +183,13 @@ __device__ uint64_t run_bound(const PlanArgs &a, const GroupInfo &gi, uint32_t r
     return a.off[gi.first + r];
 }
 
-// Runs (of run0 keys, segments) a binary step after the fan-in 4 steps
-// merges per pair: 4^steps4 2^(b - 1) for binary step b (1-based).
-__device__ uint64_t binary_unit(const GroupInfo &gi, uint32_t b) { return (1ull << (2 * gi.steps4)) << (b - 1); }
-
 // Binary jobs of pass j (1-based).
 __device__ uint32_t jobs_in(const GroupInfo &gi, uint32_t j)
 {
-    if (gi.end == gi.start || j > gi.passes || j <= gi.steps4)
+    if (gi.end == gi.start || j > gi.passes)
         return 0;
-    const uint32_t b = j - gi.steps4;
-    if (b <= gi.merges) {
-        const uint64_t span = 2 * binary_unit(gi, b);
+    if (j <= gi.merges) {
+        const uint64_t span = 1ull << j;
         return (uint32_t)((gi.nruns + span - 1) / span);
     }
     return 1;  // the copy pass
@@ -203,10 +198,13 @@ __device__ uint32_t jobs_in(const GroupInfo &gi, uint32_t j)
 // Fan-in 4 jobs of pass j (1-based): groups of four runs of 4^(j-1) run0 keys.
 __device__ uint32_t jobs4_in(const GroupInfo &gi, uint32_t j)
 {
-    if (gi.end == gi.start || j > gi.steps4)
+    if (gi.end == gi.start || j > gi.passes)
         return 0;
-    const uint64_t span = 1ull << (2 * j);
-    return (uint32_t)((gi.nruns + span - 1) / span);
+    if (j <= gi.steps4) {
+        const uint64_t span = 1ull << (2 * j);
+        return (uint32_t)((gi.nruns + span - 1) / span);
+    }
+    return 1;  // the copy pass
 }
 
 // Buffer of group gi after its pass j (0: after the block sort, segments);
@@ -240,70 +238,73 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_check(PlanArgs a, uint32_t 
         *a.status = 1;
 }
 
-// Per-group counts: x = 0 wave tiles, 1 group tiles, 2 + j binary job counts
-// of pass j, 2 + PM + j fan-in 4 job counts of pass j.
-__global__ __launch_bounds__(kPlanBlock) void k_plan_count(PlanArgs a, uint32_t arrays)
+// Both at once, by one work-group, when the offsets are few: a launch less.
+// 32768 offsets take it about as long as that launch (4 us).
+constexpr uint32_t kScanBlock = 1024;
+constexpr uint32_t kBeginMaxOffsets = 1u << 15;
+
+__global__ __launch_bounds__(kScanBlock) void k_plan_begin(PlanArgs a, uint32_t noff)
 {
-    const uint64_t t = (uint64_t)blockIdx.x * kPlanBlock + threadIdx.x;
-    const uint32_t x = (uint32_t)(t / a.G), g = (uint32_t)(t % a.G);
-    if (x >= arrays)
-        return;
-    const bool ok = *a.status == 0;
-    const GroupInfo gi = group_info(a, ok ? g : 0);
-    if (x == 0) {
-        a.bw[g] = (ok && gi.run0 == (uint32_t)kTile) ? gi.nruns : 0;
-    } else if (x == 1) {
-        a.bg[g] = (ok && gi.run0 > (uint32_t)kTile) ? gi.nruns : 0;
-    } else if (x < 2 + a.PM) {
-        const uint32_t j = x - 1;  // 1-based pass
-        a.gjob[j - 1][g] = ok ? jobs_in(gi, j) : 0;
-    } else {
-        const uint32_t j = x - 1 - a.PM;  // 1-based pass
-        a.gjob4[j - 1][g] = ok ? jobs4_in(gi, j) : 0;
+    bool bad = false;
+#pragma unroll 8
+    for (uint32_t i = threadIdx.x; i < noff; i += kScanBlock) {
+        const uint64_t x = a.off[i], y = a.off[i + 1 < noff ? i + 1 : i];
+        bad |= y < x || (i == 0 && x != 0) || (i == noff - 1 && x > a.cap);
     }
+    const int any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) {
+        *a.status = any ? 1 : 0;
+        *a.wcount = 0;
+        *a.gcount = 0;
+    }
+    for (uint32_t j = threadIdx.x; j < kMaxPlanPasses; j += kScanBlock)
+        a.tcount[j] = 0;
 }
 
-// Exclusive prefix sum of v[0, len) in place, v[len] = total (also to *total
-// when set).  One work-group per array, in chunks of kPlanBlock * kScanPer
-// elements: each thread sums kScanPer consecutive elements, the work-group
-// scans those sums, and each thread writes its elements' prefixes.
+// Exclusive prefix sum of get(0), ..., get(len - 1) into v, v[len] = total
+// (also to *total when set), by one work-group in chunks of kScanBlock *
+// kScanPer elements: each thread sums kScanPer consecutive elements, the
+// waves scan those sums, and each thread writes its elements' prefixes.
+// get(i) may read v[i].
 constexpr uint32_t kScanPer = 4;
 
-__device__ void block_scan(uint32_t *v, uint32_t len, uint32_t *total)
+template <class Get>
+__device__ void block_scan(uint32_t *v, uint32_t len, uint32_t *total, const Get &get)
 {
-    __shared__ uint32_t sh[kPlanBlock];
-    __shared__ uint32_t carry;
-    if (threadIdx.x == 0)
-        carry = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < len; base += kPlanBlock * kScanPer) {
+    __shared__ uint32_t wtot[kScanBlock / kWave];
+    const uint32_t lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    uint32_t carry = 0;  // the same in every thread
+    for (uint32_t base = 0; base < len; base += kScanBlock * kScanPer) {
         const uint32_t i0 = base + threadIdx.x * kScanPer;
         uint32_t x[kScanPer], sum = 0;
 #pragma unroll
         for (uint32_t e = 0; e < kScanPer; ++e) {
-            x[e] = i0 + e < len ? v[i0 + e] : 0;
+            x[e] = i0 + e < len ? get(i0 + e) : 0;
             sum += x[e];
         }
-        sh[threadIdx.x] = sum;
-        __syncthreads();
-        for (uint32_t d = 1; d < kPlanBlock; d <<= 1) {
-            const uint32_t y = threadIdx.x >= d ? sh[threadIdx.x - d] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += y;
-            __syncthreads();
+        uint32_t incl = sum;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)incl, d);
+            incl += lane >= (uint32_t)d ? y : 0;
         }
-        const uint32_t incl = sh[threadIdx.x];
-        const uint32_t c = carry;
-        uint32_t run = c + incl - sum;  // prefix of this thread's first element
+        if (lane == kWave - 1)
+            wtot[wave] = incl;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kScanBlock / kWave; ++w) {
+            before += w < wave ? wtot[w] : 0;
+            all += wtot[w];
+        }
+        uint32_t run = carry + before + incl - sum;  // prefix of this thread's first element
 #pragma unroll
         for (uint32_t e = 0; e < kScanPer; ++e) {
             if (i0 + e < len)
                 v[i0 + e] = run;
             run += x[e];
         }
-        __syncthreads();
-        if (threadIdx.x == kPlanBlock - 1)
-            carry = c + incl;
+        carry += all;
         __syncthreads();
     }
     if (threadIdx.x == 0) {
@@ -313,19 +314,23 @@ __device__ void block_scan(uint32_t *v, uint32_t len, uint32_t *total)
     }
 }
 
-// Scans of the per-group counts: block y = 0 wave tiles, 1 group tiles,
-// 2 + j the binary job counts of pass j, 2 + PM + j the fan-in 4 ones.
-__global__ __launch_bounds__(kPlanBlock) void k_plan_scan_groups(PlanArgs a, uint32_t first_array)
+// Counts per group and their prefix sums, one work-group per array: x = 0 wave
+// tiles, 1 group tiles (segments), 2 + j binary jobs of pass j, 2 + PM + j
+// fan-in 4 jobs of pass j.
+__global__ __launch_bounds__(kScanBlock) void k_plan_groups(PlanArgs a, uint32_t first_array)
 {
     const uint32_t x = blockIdx.x + first_array;
-    if (x == 0)
-        block_scan(a.bw, a.G, a.wcount);
-    else if (x == 1)
-        block_scan(a.bg, a.G, a.gcount);
-    else if (x < 2 + a.PM)
-        block_scan(a.gjob[x - 2], a.G, nullptr);
-    else
-        block_scan(a.gjob4[x - 2 - a.PM], a.G, nullptr);
+    const bool ok = *a.status == 0;
+    uint32_t *v = x == 0 ? a.bw : x == 1 ? a.bg : x < 2 + a.PM ? a.gjob[x - 2] : a.gjob4[x - 2 - a.PM];
+    uint32_t *total = x == 0 ? a.wcount : x == 1 ? a.gcount : nullptr;
+    block_scan(v, a.G, total, [&](uint32_t g) -> uint32_t {
+        if (!ok)
+            return 0;
+        const GroupInfo gi = group_info(a, g);
+        if (x < 2)
+            return (gi.run0 > (uint32_t)kTile) == (x == 1) ? gi.nruns : 0;
+        return x < 2 + a.PM ? jobs_in(gi, x - 1) : jobs4_in(gi, x - 1 - a.PM);
+    });
 }
 
 // Largest i in [0, n) with v[i] <= x (v nondecreasing, v[0] <= x).
@@ -342,12 +347,9 @@ __device__ uint32_t upper_index(const uint32_t *v, uint32_t n, uint32_t x)
     return lo;
 }
 
-// Block-sort tiles (segments): slot t of the wave (y = 0) or group (y = 1)
-// list.
-__global__ __launch_bounds__(kPlanBlock) void k_plan_block_tiles(PlanArgs a)
+// Block-sort tiles (segments): slot t of the wave or group list.
+__device__ void plan_block_tile(const PlanArgs &a, bool group, uint32_t t)
 {
-    const uint32_t t = blockIdx.x * kPlanBlock + threadIdx.x;
-    const bool group = blockIdx.y == 1;
     const uint32_t *pre = group ? a.bg : a.bw;
     if (t >= (group ? a.gb : a.wb) || t >= pre[a.G])
         return;
@@ -376,8 +378,8 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_jobs(PlanArgs a)
     const GroupInfo gi = group_info(a, g);
     const uint32_t pass = j + 1;
     MergeJob m;
-    if (pass - gi.steps4 <= gi.merges) {  // pass > steps4: binary jobs exist only then
-        const uint64_t half = binary_unit(gi, pass - gi.steps4), span = 2 * half;
+    if (pass <= gi.merges) {
+        const uint64_t half = 1ull << j, span = 2 * half;  // runs of run0 keys
         const uint64_t r0 = q * span;
         const uint32_t rm = (uint32_t)min<uint64_t>(r0 + half, gi.nruns);
         const uint32_t r1 = (uint32_t)min<uint64_t>(r0 + span, gi.nruns);
@@ -398,13 +400,13 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_jobs(PlanArgs a)
 }
 
 // Tile counts of every pass's jobs -> first tiles (one work-group per pass).
-__global__ __launch_bounds__(kPlanBlock) void k_plan_scan_jobs(PlanArgs a)
+__global__ __launch_bounds__(kScanBlock) void k_plan_scan_jobs(PlanArgs a)
 {
     const uint32_t j = blockIdx.x;
     const uint32_t njobs = min(a.gjob[j][a.G], a.jb[j]);
-    block_scan(a.jtile[j], njobs, a.tcount + j);
+    block_scan(a.jtile[j], njobs, a.tcount + j, [&](uint32_t i) { return a.jtile[j][i]; });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < njobs; i += kPlanBlock)
+    for (uint32_t i = threadIdx.x; i < njobs; i += kScanBlock)
         a.jobs[j][i].first_tile = a.jtile[j][i];
     if (threadIdx.x == 0 && a.tcount[j] > a.tb[j])
         a.tcount[j] = a.tb[j];  // never more tiles than the launches cover
@@ -421,13 +423,11 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_tile_map(PlanArgs a)
     a.tjob[j][t] = upper_index(a.jtile[j], njobs, t);
 }
 
-// Fan-in 4 jobs of every pass: thread (j, slot) builds job `slot` of pass j
-// (four runs of 4^j run0 / 4 keys of its segment) and its counts of cut
-// searches, item slots and cut records.
-__global__ __launch_bounds__(kPlanBlock) void k_plan_jobs4(PlanArgs a)
+// Fan-in 4 job `slot` of pass j (0-based; four runs of 4^j runs each of its
+// group, or the whole group to copy) and its counts of cut searches, item
+// slots and cut records.
+__device__ void plan_job4(const PlanArgs &a, uint32_t j, uint32_t slot)
 {
-    const uint32_t j = blockIdx.y;  // 0-based pass
-    const uint32_t slot = blockIdx.x * kPlanBlock + threadIdx.x;
     const uint32_t *pre = a.gjob4[j];
     const uint32_t total = min(pre[a.G], a.j4b[j]);
     if (slot >= total)
@@ -439,7 +439,8 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_jobs4(PlanArgs a)
     const uint64_t unit = 1ull << (2 * j), span = 4 * unit;  // runs of run0 keys
     uint64_t b[5];
     for (int t = 0; t <= 4; ++t)
-        b[t] = run_bound(a, gi, (uint32_t)min<uint64_t>(q * span + t * unit, gi.nruns));
+        b[t] = pass <= gi.steps4 ? run_bound(a, gi, (uint32_t)min<uint64_t>(q * span + t * unit, gi.nruns))
+                                 : (t ? gi.end : gi.start);
     Merge4Job m;
     m.start = b[0];
     for (int t = 0; t < 4; ++t)
@@ -449,28 +450,41 @@ __global__ __launch_bounds__(kPlanBlock) void k_plan_jobs4(PlanArgs a)
     m.src = pass == 1 ? (gi.run0 ? buf_after(gi, 0) : (uint16_t)kBufIn) : buf_after(gi, pass - 1);
     m.dst = buf_after(gi, pass);
     a.jobs4[j][slot] = m;
-    const uint32_t J = merge4_ab_segments((uint64_t)m.n[0] + m.n[1]), M = merge4_cd_cuts((uint64_t)m.n[2] + m.n[3]);
+    const uint64_t ncd = (uint64_t)m.n[2] + m.n[3];
+    const uint32_t J = merge4_ab_segments((uint64_t)m.n[0] + m.n[1], ncd), M = merge4_cd_cuts(ncd);
     a.jt4[j][slot] = merge4_tasks(J, M);
     a.ji4[j][slot] = merge4_items(J, M);
     a.jr4[j][slot] = merge4_records(J, M);
+}
+
+// The block-sort tiles (segments: rows 0 and 1 of the grid) and the fan-in 4
+// jobs of every pass (the other rows).
+__global__ __launch_bounds__(kPlanBlock) void k_plan_tables(PlanArgs a)
+{
+    const uint32_t t = blockIdx.x * kPlanBlock + threadIdx.x, y = blockIdx.y;
+    const uint32_t rows = a.kind == kKindSegments ? 2 : 0;
+    if (y < rows)
+        plan_block_tile(a, y == 1, t);
+    else
+        plan_job4(a, y - rows, t);
 }
 
 // The fan-in 4 jobs' first search, item slot and cut record of every pass
 // (one work-group per pass), and the pass's counts.  Counts past the bounds
 // the launches and areas were sized for (never, by the bounds' construction)
 // leave the pass with no job: nothing is read or written out of range.
-__global__ __launch_bounds__(kPlanBlock) void k_plan_scan_jobs4(PlanArgs a)
+__global__ __launch_bounds__(kScanBlock) void k_plan_scan_jobs4(PlanArgs a)
 {
     const uint32_t j = blockIdx.x;
     const uint32_t njobs = min(a.gjob4[j][a.G], a.j4b[j]);
     __shared__ uint32_t tot[3];
-    block_scan(a.jt4[j], njobs, &tot[0]);
+    block_scan(a.jt4[j], njobs, &tot[0], [&](uint32_t i) { return a.jt4[j][i]; });
     __syncthreads();
-    block_scan(a.ji4[j], njobs, &tot[1]);
+    block_scan(a.ji4[j], njobs, &tot[1], [&](uint32_t i) { return a.ji4[j][i]; });
     __syncthreads();
-    block_scan(a.jr4[j], njobs, &tot[2]);
+    block_scan(a.jr4[j], njobs, &tot[2], [&](uint32_t i) { return a.jr4[j][i]; });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < njobs; i += kPlanBlock) {
+    for (uint32_t i = threadIdx.x; i < njobs; i += kScanBlock) {
         a.jobs4[j][i].task_off = a.jt4[j][i];
         a.jobs4[j][i].item_off = a.ji4[j][i];
         a.jobs4[j][i].cut_off = a.jr4[j][i];
@@ -492,7 +506,7 @@ struct PlanSpec {
     uint32_t grun;
     bool pairs;
     uint32_t noff;  // offsets read (validity check)
-    uint32_t four;  // fan-in 4 steps (PlanArgs::four); the areas are reserved for every segmented plan
+    bool four;  // fan-in 4 steps; segmented plans reserve the areas of both fan-ins
     bool reserve_four;  // explicit runs / buckets: size the areas of both fan-ins (temp queries)
 };
 
@@ -501,30 +515,28 @@ struct PlanBounds {
     uint32_t PM;
     uint64_t wb, gb;
     uint64_t jb[kMaxPlanPasses], tb[kMaxPlanPasses];
-    // fan-in 4 steps (segments): passes, jobs per pass, and cut
-    // searches / item slots / cut records of any one pass
+    // fan-in 4 steps: passes, jobs per pass, and cut searches / item slots /
+    // cut records of any one pass
     uint32_t PM4;
     uint64_t j4b[kMaxPlan4Passes];
     uint64_t t4b, i4b, r4b;
 };
 
-// Fan-in 4 steps of a segment of `runs` runs: while more than two remain.
-uint32_t four_steps(uint64_t runs)
+// Merge levels of a group of `runs` runs, four-way or binary.
+uint32_t merge_levels(uint64_t runs, bool four)
 {
     uint32_t st = 0;
-    for (; runs > 2; runs = (runs + 3) / 4)
+    for (; runs > 1; runs = four ? (runs + 3) / 4 : (runs + 1) / 2)
         ++st;
     return st;
 }
 
-// Merge levels of a group of `runs` runs: fan-in 4 steps (when `four`) while
-// more than two remain, then binary ones.
-uint32_t merge_levels(uint64_t runs, bool four)
+// Fan-in 4 levels that a plan of segments of at most cap keys in all may take:
+// a segment has runs of grun keys, or of a tile where it is shorter than gmin.
+uint32_t segment_levels(const PlanSpec &sp, uint64_t cap)
 {
-    const uint32_t st = four ? four_steps(runs) : 0;
-    for (uint32_t i = 0; i < st; ++i)
-        runs = (runs + 3) / 4;
-    return st + clog2(std::max<uint64_t>(runs, 1));
+    const uint64_t tiles = (std::min(cap, sp.gmin) + kTile - 1) / kTile, groups = (cap + sp.grun - 1) / sp.grun;
+    return merge_levels(std::max(tiles, groups), true);
 }
 
 PlanBounds plan_bounds(const PlanSpec &sp, uint64_t cap)
@@ -542,7 +554,7 @@ PlanBounds plan_bounds(const PlanSpec &sp, uint64_t cap)
             // runs of 4^(j-1) each) at most (tiles + G) / 4^j + G jobs; a job of
             // t keys takes at most t / kAbStep + 1 searches and item slots, and
             // two more cut records
-            b.PM4 = four_steps(tiles);
+            b.PM4 = merge_levels(tiles, true);
             for (uint32_t j = 1; j <= b.PM4; ++j)
                 b.j4b[j - 1] = ((tiles + sp.G) >> (2 * j)) + sp.G + 1;
             const uint64_t most = b.PM4 ? b.j4b[0] : 0;
@@ -551,22 +563,23 @@ PlanBounds plan_bounds(const PlanSpec &sp, uint64_t cap)
         }
     } else {
         const uint32_t nr = sp.kind == kKindRuns ? sp.k : sp.s;
-        // a query reserves the binary pass count (the larger) and the fan-in 4 areas
-        const uint32_t levels = merge_levels(nr, sp.four == 1 && !sp.reserve_four);
-        if (sp.kind == kKindRuns)
-            b.PM = levels + (sp.extra_copy ? 1 : 0);
-        else
-            b.PM = std::max<uint32_t>(levels, 1);
+        // a query reserves the areas of both fan-ins; the last level of either
+        // may be a copy (buckets: of a group of one run)
+        const uint32_t levels = merge_levels(nr, false), levels4 = merge_levels(nr, true);
+        const uint32_t copy = sp.kind == kKindRuns ? (sp.extra_copy ? 1 : 0) : 0;
+        const uint32_t least = sp.kind == kKindRuns ? 0 : 1;
+        b.PM = sp.four && !sp.reserve_four ? 0 : std::max(levels + copy, least);
         for (uint32_t j = 1; j <= b.PM; ++j) {
-            // every group: at most ceil(nr / 2^j) binary jobs while merging
-            // (after fan-in 4 steps fewer), else one copy
+            // every group: at most ceil(nr / 2^j) binary jobs while merging,
+            // else one copy
             const uint64_t per = j <= levels ? ((uint64_t)nr + (1ull << j) - 1) >> j : 1;
             b.jb[j - 1] = per * sp.G;
         }
-        if ((sp.four == 1 || sp.reserve_four) && four_steps(nr) <= (uint32_t)kMaxPlan4Passes) {
-            // step j: ceil(nr / 4^j) jobs per group, every job of t keys at most
-            // t / kAbStep + 1 searches and item slots and two more cut records
-            b.PM4 = four_steps(nr);
+        if ((sp.four || sp.reserve_four) && levels4 + copy <= (uint32_t)kMaxPlan4Passes) {
+            // step j: ceil(nr / 4^j) jobs per group (a copy: one), every job of t
+            // keys at most t / kAbStep + 1 searches and item slots and two more
+            // cut records
+            b.PM4 = std::max(levels4 + copy, least);
             for (uint32_t j = 1; j <= b.PM4; ++j)
                 b.j4b[j - 1] = (((uint64_t)nr + (1ull << (2 * j)) - 1) >> (2 * j)) * sp.G + 1;
             const uint64_t most = b.PM4 ? b.j4b[0] : 0;
@@ -589,7 +602,7 @@ struct PlanLayout {
     // counts; one search map, item map and cut record area all passes share
     uint64_t gjob4[kMaxPlan4Passes], jobs4[kMaxPlan4Passes];
     uint64_t jt4[kMaxPlan4Passes], ji4[kMaxPlan4Passes], jr4[kMaxPlan4Passes], c4;
-    uint64_t tmap4, imap4, cuts4;
+    uint64_t imap4, cuts4;
     uint64_t total;
 };
 
@@ -643,8 +656,6 @@ PlanLayout plan_layout(const PlanSpec &sp, const PlanBounds &b, uint64_t cap)
         }
         L.c4 = o;
         o = a256(o + kMaxPlan4Passes * 4 * 4);
-        L.tmap4 = o;
-        o = a256(o + b.t4b * 4);
         L.imap4 = o;
         o = a256(o + b.i4b * 4);
         L.cuts4 = o;
@@ -683,14 +694,14 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
     const PlanLayout L = plan_layout(sp, b, cap);
     if (b.PM > kMaxPlanPasses || sp.G == 0)
         return BCF_ERR_INVALID;
-    for (uint32_t j = 0; j < b.PM; ++j)
+    const bool segs = sp.kind == kKindSegments;
+    // the passes to launch, of one fan-in
+    const uint32_t PM = sp.four ? 0 : b.PM, P4 = !sp.four ? 0 : segs ? segment_levels(sp, cap) : b.PM4;
+    for (uint32_t j = 0; j < PM; ++j)
         if (b.jb[j] > 0xFFFFFFFFull || b.tb[j] > 0xFFFFFFFFull)
             return BCF_ERR_INVALID;
-    if (b.PM4 > kMaxPlan4Passes || b.t4b > 0xFFFFFFFFull || b.r4b > 0xFFFFFFFFull)
+    if (P4 > b.PM4 || P4 > kMaxPlan4Passes || b.t4b > 0xFFFFFFFFull || b.r4b > 0xFFFFFFFFull)
         return BCF_ERR_INVALID;
-    // fan-in 4 launches only when some segment may take them: on, or auto with
-    // a capacity that reaches the threshold
-    const uint32_t P4 = (sp.four == 1 || (sp.four == 2 && cap >= kAutoFourWayMinN)) ? b.PM4 : 0;
     PlanArgs a{};
     a.off = off_dev;
     a.kind = sp.kind;
@@ -701,8 +712,8 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
     a.extra_copy = sp.extra_copy;
     a.gmin = sp.gmin;
     a.grun = sp.grun;
-    a.PM = b.PM;
-    a.four = P4 ? sp.four : 0;
+    a.PM = PM;
+    a.four = sp.four ? 1 : 0;
     a.PM4 = P4;
     a.cap = cap;
     a.status = reinterpret_cast<uint32_t *>(temp + L.status);
@@ -715,7 +726,7 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
     a.wcount = reinterpret_cast<uint32_t *>(temp + L.wcount);
     a.gcount = reinterpret_cast<uint32_t *>(temp + L.gcount);
     a.tcount = reinterpret_cast<uint32_t *>(temp + L.tcount);
-    for (uint32_t j = 0; j < b.PM; ++j) {
+    for (uint32_t j = 0; j < PM; ++j) {
         a.gjob[j] = reinterpret_cast<uint32_t *>(temp + L.gjob[j]);
         a.jobs[j] = reinterpret_cast<MergeJob *>(temp + L.jobs[j]);
         a.jtile[j] = reinterpret_cast<uint32_t *>(temp + L.jtile[j]);
@@ -735,54 +746,46 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
     a.t4b = (uint32_t)b.t4b;
     a.i4b = (uint32_t)b.i4b;
     a.r4b = (uint32_t)b.r4b;
-    // status, the block-tile totals and the pass totals start at zero (a small
-    // fill kernel rather than a memset: the sequence may be captured in a graph)
-    hipLaunchKernelGGL(k_plan_zero, dim3(1), dim3(64), 0, s, a);
-    BCF_PLAN_TRY(dev(hipGetLastError()));
-    {
+    // status, the block-tile totals and the pass totals start at zero (small fill
+    // kernels rather than a memset: the sequence may be captured in a graph)
+    if (sp.noff <= kBeginMaxOffsets) {
+        hipLaunchKernelGGL(k_plan_begin, dim3(1), dim3(kScanBlock), 0, s, a, sp.noff);
+        BCF_PLAN_TRY(dev(hipGetLastError()));
+    } else {
+        hipLaunchKernelGGL(k_plan_zero, dim3(1), dim3(64), 0, s, a);
+        BCF_PLAN_TRY(dev(hipGetLastError()));
         const uint32_t blocks = (sp.noff + kPlanBlock - 1) / kPlanBlock;
         hipLaunchKernelGGL(k_plan_check, dim3(blocks), dim3(kPlanBlock), 0, s, a, sp.noff);
         BCF_PLAN_TRY(dev(hipGetLastError()));
     }
-    const bool segs = sp.kind == kKindSegments;
-    const uint32_t arrays = 2 + b.PM + P4;
-    {
-        const uint64_t threads = (uint64_t)arrays * sp.G;
-        hipLaunchKernelGGL(k_plan_count, dim3((uint32_t)((threads + kPlanBlock - 1) / kPlanBlock)), dim3(kPlanBlock),
-                           0, s, a, arrays);
+    const uint32_t arrays = 2 + PM + P4, first = segs ? 0 : 2;
+    if (arrays > first) {  // nothing to count when no pass is planned (a lone run merged in place)
+        hipLaunchKernelGGL(k_plan_groups, dim3(arrays - first), dim3(kScanBlock), 0, s, a, first);
         BCF_PLAN_TRY(dev(hipGetLastError()));
-        const uint32_t first = segs ? 0 : 2;
-        if (arrays > first) {  // nothing to scan when no pass is planned (a lone run merged in place)
-            hipLaunchKernelGGL(k_plan_scan_groups, dim3(arrays - first), dim3(kPlanBlock), 0, s, a, first);
-            BCF_PLAN_TRY(dev(hipGetLastError()));
-        }
     }
-    if (segs) {
-        const uint64_t most = std::max(b.wb, b.gb);
-        hipLaunchKernelGGL(k_plan_block_tiles, dim3((uint32_t)((most + kPlanBlock - 1) / kPlanBlock), 2),
+    if (segs || P4) {
+        const uint64_t most = std::max(segs ? std::max(b.wb, b.gb) : 1, P4 ? b.j4b[0] : 1);
+        hipLaunchKernelGGL(k_plan_tables, dim3((uint32_t)((most + kPlanBlock - 1) / kPlanBlock), (segs ? 2 : 0) + P4),
                            dim3(kPlanBlock), 0, s, a);
         BCF_PLAN_TRY(dev(hipGetLastError()));
     }
-    if (b.PM) {
+    if (PM) {
         uint64_t mj = 1, mt = 1;
-        for (uint32_t j = 0; j < b.PM; ++j) {
+        for (uint32_t j = 0; j < PM; ++j) {
             mj = std::max(mj, b.jb[j]);
             mt = std::max(mt, b.tb[j]);
         }
-        hipLaunchKernelGGL(k_plan_jobs, dim3((uint32_t)((mj + kPlanBlock - 1) / kPlanBlock), b.PM), dim3(kPlanBlock),
-                           0, s, a);
+        hipLaunchKernelGGL(k_plan_jobs, dim3((uint32_t)((mj + kPlanBlock - 1) / kPlanBlock), PM), dim3(kPlanBlock), 0, s,
+                           a);
         BCF_PLAN_TRY(dev(hipGetLastError()));
-        hipLaunchKernelGGL(k_plan_scan_jobs, dim3(b.PM), dim3(kPlanBlock), 0, s, a);
+        hipLaunchKernelGGL(k_plan_scan_jobs, dim3(PM), dim3(kScanBlock), 0, s, a);
         BCF_PLAN_TRY(dev(hipGetLastError()));
-        hipLaunchKernelGGL(k_plan_tile_map, dim3((uint32_t)((mt + kPlanBlock - 1) / kPlanBlock), b.PM),
-                           dim3(kPlanBlock), 0, s, a);
+        hipLaunchKernelGGL(k_plan_tile_map, dim3((uint32_t)((mt + kPlanBlock - 1) / kPlanBlock), PM), dim3(kPlanBlock), 0,
+                           s, a);
         BCF_PLAN_TRY(dev(hipGetLastError()));
     }
     if (P4) {
-        hipLaunchKernelGGL(k_plan_jobs4, dim3((uint32_t)((b.j4b[0] + kPlanBlock - 1) / kPlanBlock), P4),
-                           dim3(kPlanBlock), 0, s, a);
-        BCF_PLAN_TRY(dev(hipGetLastError()));
-        hipLaunchKernelGGL(k_plan_scan_jobs4, dim3(P4), dim3(kPlanBlock), 0, s, a);
+        hipLaunchKernelGGL(k_plan_scan_jobs4, dim3(P4), dim3(kScanBlock), 0, s, a);
         BCF_PLAN_TRY(dev(hipGetLastError()));
     }
     const bool pairs = sp.pairs;
@@ -801,20 +804,18 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
         }
     }
     uint32_t *splits = reinterpret_cast<uint32_t *>(temp + L.splits);
-    uint32_t *tmap4 = reinterpret_cast<uint32_t *>(temp + L.tmap4);
     uint32_t *imap4 = reinterpret_cast<uint32_t *>(temp + L.imap4);
-    for (uint32_t j = 0; j < b.PM; ++j) {
-        // the fan-in 4 jobs of the pass (segments still taking fan-in 4 steps),
-        // then its binary jobs (the other segments); they touch disjoint ranges
-        for (int phase = 0; j < P4 && phase < 3; ++phase) {
-            static const char *const names[2][3] = {{"map4_keys_table", "cuts4_keys_table", "merge4_keys_table"},
-                                                    {"map4_pairs_table", "cuts4_pairs_table", "merge4_pairs_table"}};
-            void *p = prof_begin(names[sp.pairs][phase], s, 0.0);
-            const hipError_t e = launch_merge4_table(kb, a.jobs4[j], a.j4b[j], tmap4, a.t4b, imap4, a.i4b,
-                                                     temp + L.cuts4, cap, phase, s, a.c4[j], vb);
+    for (uint32_t j = 0; j < P4; ++j)
+        for (int phase = 0; phase < 2; ++phase) {
+            static const char *const names[2][2] = {{"cuts4_keys_table", "merge4_keys_table"},
+                                                    {"cuts4_pairs_table", "merge4_pairs_table"}};
+            void *p = prof_begin(names[pairs][phase], s, 0.0);
+            const hipError_t e = launch_merge4_table(kb, a.jobs4[j], a.j4b[j], a.t4b, imap4, a.i4b, temp + L.cuts4, cap,
+                                                     phase == 1, s, a.c4[j], vb);
             prof_end(p);
             BCF_PLAN_TRY(dev(e));
         }
+    for (uint32_t j = 0; j < PM; ++j)
         for (int phase = 0; phase < 2; ++phase) {
             const bool part = phase == 0;
             void *p = prof_begin(part ? kname_partition(pairs, true) : kname_merge(pairs, true), s, 0.0);
@@ -823,7 +824,6 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
             prof_end(p);
             BCF_PLAN_TRY(dev(e));
         }
-    }
     return BCF_OK;
 }
 
@@ -870,17 +870,25 @@ bcf_status planned_call(const PlanSpec &worst, const PlanSpec &actual, const uin
 
 uint64_t seg_group_min(bool pairs, uint64_t knob) { return knob ? knob : group_run_keys(pairs) / 2; }
 
-// Fan-in 4 steps for the merges of explicit runs (bcf_merge_runs) or of the
-// buckets of the sort by distribution, groups of nr runs: tuning knob
-// merge_fan_in 4 on, 2 off, 0 (auto) from 16 runs per group (decided on the
-// host, which does not know the key count: 2^20 keys in 8 runs merge in
-// 0.146 ms binary against 0.166 ms four-way, 2^24 keys in 16 runs alike, 2^26
-// keys in 16 / 256 / 4096 runs 0.72 / 1.30 / 1.77 ms binary against 0.58 /
-// 1.02 / 1.41 ms); never for more runs than kMaxPlan4Passes steps reduce.
+// Fan-in 4 steps unless the tuning asks for binary ones; for explicit runs
+// never for more runs than kMaxPlan4Passes steps (a copy among them) reduce.
+bool segs_four_way() { return tuning().merge_fan_in != 2; }
 bool runs_four_way(uint32_t nr)
 {
-    const int f = tuning().merge_fan_in;
-    return (f == 4 || (f == 0 && nr >= 16)) && four_steps(nr) <= (uint32_t)kMaxPlan4Passes;
+    return tuning().merge_fan_in != 2 && merge_levels(nr, true) + 1 <= (uint32_t)kMaxPlan4Passes;
+}
+
+PlanSpec segments_spec(bool pairs, uint32_t nseg)
+{
+    PlanSpec sp{};
+    sp.kind = kKindSegments;
+    sp.G = nseg;
+    sp.gmin = seg_group_min(pairs, tuning().group_min_keys);
+    sp.grun = group_run_keys(pairs);
+    sp.pairs = pairs;
+    sp.noff = nseg + 1;
+    sp.four = segs_four_way();
+    return sp;
 }
 
 bcf_status segmented_device(bool pairs, const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
@@ -895,16 +903,30 @@ bcf_status segmented_device(bool pairs, const uint32_t *kin, const uint32_t *vin
     }
     if (!off)
         return BCF_ERR_INVALID;
-    PlanSpec sp{};
-    sp.kind = kKindSegments;
-    sp.G = nseg;
-    sp.gmin = seg_group_min(pairs, tuning().group_min_keys);
-    sp.grun = group_run_keys(pairs);
-    sp.pairs = pairs;
-    sp.noff = nseg + 1;
-    const int fan_in = tuning().merge_fan_in;
-    sp.four = fan_in == 4 ? 1u : (fan_in == 0 ? 2u : 0u);
+    const PlanSpec sp = segments_spec(pairs, nseg);
     return planned_call(sp, sp, off, kin, vin, kout, vout, temp, temp_bytes, s);
+}
+
+PlanSpec runs_spec(bool pairs, uint32_t k)
+{
+    PlanSpec sp{};
+    sp.kind = kKindRuns;
+    sp.G = 1;
+    sp.k = k;
+    sp.pairs = pairs;
+    sp.noff = k + 1;
+    sp.four = runs_four_way(k);
+    return sp;
+}
+
+// The plan that a temp size is reserved for: it depends neither on whether the
+// call is in place nor on the fan-in.
+PlanSpec reserved(PlanSpec sp)
+{
+    sp.extra_copy = 1;
+    sp.four = false;
+    sp.reserve_four = true;
+    return sp;
 }
 
 }  // namespace
@@ -929,20 +951,9 @@ bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, cons
     if (!run_offsets || k == 0xFFFFFFFFu)
         return BCF_ERR_INVALID;
     const bool pairs = vals_in != nullptr;
-    const bool four = runs_four_way(k);
-    const uint32_t merges = merge_levels(k, four);
-    PlanSpec sp{};
-    sp.kind = kKindRuns;
-    sp.G = 1;
-    sp.k = k;
-    sp.pairs = pairs;
-    sp.noff = k + 1;
-    sp.four = four ? 1u : 0u;
-    PlanSpec worst = sp;
-    // the temp size depends neither on whether the call is in place nor on the fan-in
-    worst.extra_copy = 1;
-    worst.four = 0;
-    worst.reserve_four = true;
+    PlanSpec sp = runs_spec(pairs, k);
+    const uint32_t merges = merge_levels(k, sp.four);
+    const PlanSpec worst = reserved(sp);
     const bool inplace = keys_in == keys_out || (pairs && vals_in == vals_out);
     // in place, a run count whose merge levels are odd would make the first pass
     // read and write the output: one more pass copies the result from temp; a
@@ -969,6 +980,22 @@ bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, cons
             return BCF_ERR_UNSORTED_RUN;
     }
     return planned_call(worst, sp, run_offsets, keys_in, vals_in, keys_out, vals_out, temp, temp_bytes, s);
+}
+
+bcf_status bcf_merge_runs_temp(uint64_t n, uint32_t k, int pairs, uint64_t *temp_bytes)
+{
+    if (!temp_bytes || n > kMaxKeys || k == 0xFFFFFFFFu)
+        return BCF_ERR_INVALID;
+    *temp_bytes = k ? plan_need(reserved(runs_spec(pairs != 0, k)), n) : 0;
+    return BCF_OK;
+}
+
+bcf_status bcf_segmented_sort_temp(uint64_t n, uint32_t nseg, int pairs, uint64_t *temp_bytes)
+{
+    if (!temp_bytes || n > kMaxKeys)
+        return BCF_ERR_INVALID;
+    *temp_bytes = nseg ? plan_need(segments_spec(pairs != 0, nseg), n) : 0;
+    return BCF_OK;
 }
 
 bcf_status bcf_segmented_sort(const uint32_t *keys_in, uint32_t *keys_out, const uint64_t *seg_offsets, uint32_t nseg,
@@ -1018,11 +1045,8 @@ bcf_status bcf_sort_u32_pb(const uint32_t *keys_in, uint32_t *keys_out, uint64_t
     sp.s = s;
     sp.pivot = pivot_buckets ? 1 : 0;
     sp.noff = nb * s + 1;
-    sp.four = runs_four_way(s) ? 1u : 0u;
-    PlanSpec worst = sp;  // the temp size does not depend on the fan-in
-    worst.four = 0;
-    worst.reserve_four = true;
-    const uint64_t need_merge = plan_need(worst, n);
+    sp.four = runs_four_way(s);
+    const uint64_t need_merge = plan_need(reserved(sp), n);  // whatever the fan-in
     const uint64_t d_bytes = a256(n * 4), p_bytes = a256(((uint64_t)nb * s + 1) * 8);
     const uint64_t scratch = std::max(need_runs, std::max(need_dist, need_merge));
     const uint64_t need = d_bytes + p_bytes + scratch;
