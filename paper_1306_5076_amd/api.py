@@ -341,15 +341,13 @@ def _planned(fn, fname, keys, off, vals, keys_out, vals_out, stream, workspace, 
     if vals is not None and vals_out is None:
         vals_out = torch.empty_like(vals)
     stream, sh = _stream(stream, keys.device)
+    # sized by the keys there are: asking the entry point would read the last
+    # offset back and wait for the stream on every call
     need = ctypes.c_uint64(0)
-    vdummy = ctypes.c_void_p(1) if vals is not None else None
-    if merge:
-        check(fname, fn(None, vdummy, _ptr(off), k, None, None, None, ctypes.byref(need), sh))
-    elif vals is None:
-        check(fname, fn(None, None, _ptr(off), k, None, ctypes.byref(need), sh))
-    else:
-        check(fname, fn(None, None, None, None, _ptr(off), k, None, ctypes.byref(need), sh))
-    temp, tb = _temp(workspace, need.value, keys.device, stream)
+    size = load().bcf_merge_runs_temp if merge else load().bcf_segmented_sort_temp
+    check(fname, size(min(keys.numel(), 0xFFFFFFFF), max(k, 0), int(vals is not None), ctypes.byref(need)))
+    temp, _ = _temp(workspace, need.value, keys.device, stream)
+    tb = need  # the capacity follows from it: a workspace may be larger than these keys
     if keys.numel() and k:
         tp = _ptr(temp) or ctypes.c_void_p(1)
         if merge:
