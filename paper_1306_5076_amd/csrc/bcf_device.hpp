@@ -479,6 +479,28 @@ __device__ __forceinline__ void split_halves(const double (&x)[kLine], uint32_t 
     }
 }
 
+__device__ __forceinline__ void split_halves(const uint64_t (&x)[kLine], uint32_t (&hi)[kLine], uint32_t (&lo)[kLine])
+{
+#pragma unroll
+    for (int r = 0; r < kLine; ++r) {
+        hi[r] = (uint32_t)(x[r] >> 32);
+        lo[r] = (uint32_t)x[r];
+    }
+}
+__device__ __forceinline__ void join_halves(double (&x)[kLine], const uint32_t (&hi)[kLine], const uint32_t (&lo)[kLine])
+{
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+}
+__device__ __forceinline__ void join_halves(uint64_t (&x)[kLine], const uint32_t (&hi)[kLine],
+                                            const uint32_t (&lo)[kLine])
+{
+#pragma unroll
+    for (int r = 0; r < kLine; ++r)
+        x[r] = ((uint64_t)hi[r] << 32) | lo[r];
+}
+
 // The same for 64-bit elements, one 32-bit half at a time (each half keeps the
 // conflict-free word pattern of the 32-bit exchange).
 template <int WS, int RS>
@@ -628,34 +650,47 @@ __device__ __forceinline__ void to_strided_half(Lines<false> &t, uint32_t *lds, 
 
 // The same two transposes for 64-bit elements, one 32-bit half after the
 // other through the same matrices.
-__device__ __forceinline__ void to_blocked_half(Lines<true> &t, uint32_t *lds, uint32_t lane)
+template <class E>
+__device__ __forceinline__ void to_blocked_half_wide(E (&x)[kLine], uint32_t *lds, uint32_t lane)
 {
     uint32_t hi[kLine], lo[kLine];
-    split_halves(t.e, hi, lo);
+    split_halves(x, hi, lo);
     swap_quadrants(hi);
     half_block_transpose<0, true>(hi, lds, lane);
     half_block_transpose<kLine / 2, true>(hi, lds, lane);
     swap_quadrants(lo);
     half_block_transpose<0, true>(lo, lds, lane);
     half_block_transpose<kLine / 2, true>(lo, lds, lane);
-#pragma unroll
-    for (int r = 0; r < kLine; ++r)
-        t.e[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+    join_halves(x, hi, lo);
 }
-
-__device__ __forceinline__ void to_strided_half(Lines<true> &t, uint32_t *lds, uint32_t lane)
+template <class E>
+__device__ __forceinline__ void to_strided_half_wide(E (&x)[kLine], uint32_t *lds, uint32_t lane)
 {
     uint32_t hi[kLine], lo[kLine];
-    split_halves(t.e, hi, lo);
+    split_halves(x, hi, lo);
     half_block_transpose<0, false>(hi, lds, lane);
     half_block_transpose<kLine / 2, false>(hi, lds, lane);
     swap_quadrants(hi);
     half_block_transpose<0, false>(lo, lds, lane);
     half_block_transpose<kLine / 2, false>(lo, lds, lane);
     swap_quadrants(lo);
-#pragma unroll
-    for (int r = 0; r < kLine; ++r)
-        t.e[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+    join_halves(x, hi, lo);
+}
+__device__ __forceinline__ void to_blocked_half(Lines<true> &t, uint32_t *lds, uint32_t lane)
+{
+    to_blocked_half_wide(t.e, lds, lane);
+}
+__device__ __forceinline__ void to_strided_half(Lines<true> &t, uint32_t *lds, uint32_t lane)
+{
+    to_strided_half_wide(t.e, lds, lane);
+}
+__device__ __forceinline__ void to_blocked_half(Lines64 &t, uint32_t *lds, uint32_t lane)
+{
+    to_blocked_half_wide(t.e, lds, lane);
+}
+__device__ __forceinline__ void to_strided_half(Lines64 &t, uint32_t *lds, uint32_t lane)
+{
+    to_strided_half_wide(t.e, lds, lane);
 }
 
 // ------------------------------------------------------ group (multi-wave) sort
@@ -917,89 +952,99 @@ __device__ __forceinline__ void sort_tile_keys(Lines<false> &t, uint32_t *lds, u
     half_clean_lines<kLine / 2, -1>(t);
 }
 
-// The same sort of a wave tile of key/value elements: a stage between lanes takes
-// two moves, a comparison and two selects per element (five VALU instructions
-// against two for a key), which still undercuts the two transposes of both
-// 32-bit halves that a round through the LDS costs.
+// The same sort of a wave tile of 64-bit elements, key/value ones or u64 keys: a
+// stage between lanes takes two moves, a comparison and two selects per element
+// (five VALU instructions against two for a key), which still undercuts the
+// two transposes of both 32-bit halves that a round through the LDS costs.
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_move(uint64_t x)
+{
+    const uint32_t hi = dpp_move<CTRL>((uint32_t)(x >> 32)), lo = dpp_move<CTRL>((uint32_t)x);
+    return ((uint64_t)hi << 32) | lo;
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_move(double x)
 {
-    const uint64_t b = bits_of(x);
-    const uint32_t hi = dpp_move<CTRL>((uint32_t)(b >> 32)), lo = dpp_move<CTRL>((uint32_t)b);
-    return elem_of(((uint64_t)hi << 32) | lo);
+    return elem_of(dpp_move<CTRL>(bits_of(x)));
 }
 
 // The smaller of x and y, or the larger; equal elements are alike in every bit.
-__device__ __forceinline__ double keep_elem(double x, double y, bool larger) { return ((x < y) != larger) ? x : y; }
+template <class E>
+__device__ __forceinline__ E keep_elem(E x, E y, bool larger)
+{
+    return ((x < y) != larger) ? x : y;
+}
 
-template <int CTRL>
-__device__ __forceinline__ void lane_clean(Lines<true> &t, bool larger)
+template <int CTRL, class E>
+__device__ __forceinline__ void lane_clean(E (&x)[kLine], bool larger)
 {
 #pragma unroll
     for (int r = 0; r < kLine; ++r)
-        t.e[r] = keep_elem(t.e[r], dpp_move<CTRL>(t.e[r]), larger);
+        x[r] = keep_elem(x[r], dpp_move<CTRL>(x[r]), larger);
 }
 
-template <int CTRL>
-__device__ __forceinline__ void lane_clean_mirrored(Lines<true> &t, bool larger)
+template <int CTRL, class E>
+__device__ __forceinline__ void lane_clean_mirrored(E (&x)[kLine], bool larger)
 {
 #pragma unroll
     for (int r = 0; r < kLine / 2; ++r) {
-        const double a = t.e[r], b = t.e[kLine - 1 - r];
-        t.e[r] = keep_elem(a, dpp_move<CTRL>(b), larger);
-        t.e[kLine - 1 - r] = keep_elem(b, dpp_move<CTRL>(a), larger);
+        const E a = x[r], b = x[kLine - 1 - r];
+        x[r] = keep_elem(a, dpp_move<CTRL>(b), larger);
+        x[kLine - 1 - r] = keep_elem(b, dpp_move<CTRL>(a), larger);
     }
 }
 
-template <int J>
-__device__ __forceinline__ void blocked_to_split(double (&x)[kLine], uint32_t *lds, uint32_t lane)
+template <int J, class E>
+__device__ __forceinline__ void blocked_to_split_wide(E (&x)[kLine], uint32_t *lds, uint32_t lane)
 {
     uint32_t hi[kLine], lo[kLine];
     split_halves(x, hi, lo);
     blocked_to_split<J>(hi, lds, lane);
     blocked_to_split<J>(lo, lds, lane);
-#pragma unroll
-    for (int r = 0; r < kLine; ++r)
-        x[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+    join_halves(x, hi, lo);
 }
 
-__device__ __forceinline__ void split_to_blocked(double (&x)[kLine], uint32_t *lds, uint32_t lane)
+template <class E>
+__device__ __forceinline__ void split_to_blocked_wide(E (&x)[kLine], uint32_t *lds, uint32_t lane)
 {
     uint32_t hi[kLine], lo[kLine];
     split_halves(x, hi, lo);
     split_to_blocked(hi, lds, lane);
     split_to_blocked(lo, lds, lane);
-#pragma unroll
-    for (int r = 0; r < kLine; ++r)
-        x[r] = elem_of(((uint64_t)hi[r] << 32) | lo[r]);
+    join_halves(x, hi, lo);
 }
 
-__device__ __forceinline__ void sort_tile_pairs(Lines<true> &t, uint32_t *lds, uint32_t lane)
+// The element in reversed order (see flip).
+__device__ __forceinline__ double complement(double x) { return elem_of(bits_of(x) ^ kPayloadMask); }
+__device__ __forceinline__ uint64_t complement(uint64_t x) { return ~x; }
+
+template <class L>
+__device__ __forceinline__ void sort_tile_wide(L &t, uint32_t *lds, uint32_t lane)
 {
     flip(t, lane >> 5);
     oe_sort_lines<0, kLine - 1>(t);
     const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-    lane_clean_mirrored<kDppXor1>(t, b0);
+    lane_clean_mirrored<kDppXor1>(t.e, b0);
     half_clean_lines<kLine / 2, -1>(t);
-    lane_clean_mirrored<kDppXor3>(t, b1);
-    lane_clean<kDppXor1>(t, b0);
+    lane_clean_mirrored<kDppXor3>(t.e, b1);
+    lane_clean<kDppXor1>(t.e, b0);
     half_clean_lines<kLine / 2, -1>(t);
-    lane_clean_mirrored<kDppXor7>(t, b2);
-    lane_clean<kDppXor2>(t, b1);
-    lane_clean<kDppXor1>(t, b0);
+    lane_clean_mirrored<kDppXor7>(t.e, b2);
+    lane_clean<kDppXor2>(t.e, b1);
+    lane_clean<kDppXor1>(t.e, b0);
     half_clean_lines<kLine / 2, -1>(t);
-    blocked_to_split<4>(t.e, lds, lane);
+    blocked_to_split_wide<4>(t.e, lds, lane);
     half_clean_lines<8, -1>(t);
-    split_to_blocked(t.e, lds, lane);
+    split_to_blocked_wide(t.e, lds, lane);
     half_clean_lines<kLine / 2, -1>(t);
-    blocked_to_split<5>(t.e, lds, lane);
+    blocked_to_split_wide<5>(t.e, lds, lane);
     half_clean_lines<16, -1>(t);
-    split_to_blocked(t.e, lds, lane);
+    split_to_blocked_wide(t.e, lds, lane);
     half_clean_lines<kLine / 2, -1>(t);
     to_strided_half(t, lds, lane);
 #pragma unroll
     for (int r = kLine / 2; r < kLine; ++r)
-        t.e[r] = elem_of(bits_of(t.e[r]) ^ kPayloadMask);
+        t.e[r] = complement(t.e[r]);
     half_clean_lines<kLine / 2, -1>(t);
     to_blocked_half(t, lds, lane);
     half_clean_lines<kLine / 2, -1>(t);

@@ -773,7 +773,7 @@ __device__ __forceinline__ void wave_tile(Lines<P> &a, const SortItem &it, const
     if constexpr (SHEAR)
         shear_sort_blocked<P>(a, lds, lane);
     else if (uniform(it.count) != 0)  // always; a block of its own, which the load's registers do not reach into
-        sort_tile_pairs(a, lds, lane);
+        sort_tile_wide(a, lds, lane);
     write_samples<P>(a, src.out_smp, src.pos(t), it.count, lane);
     to_strided(a, lds, lane);
     if constexpr (P) {
@@ -922,7 +922,7 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(2))) 
         load_elems(t, uniform(it.ks), count, ln, wave * kTile, src);
         if (count != 0) {   // else padding only
             flip(t, wave);  // odd sub-tiles descending
-            sort_tile_pairs(t, own, ln);
+            sort_tile_wide(t, own, ln);
             flip(t, wave);
         }
         // the rounds the group needs: later ones would merge with padding only

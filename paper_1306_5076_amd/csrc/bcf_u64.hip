@@ -13,13 +13,11 @@
 //   sorted sub-tiles in two more rounds through the shared CROSS layout (the
 //   group tiles of the 32-bit sort), for runs of 16384 keys: two merge passes
 //   fewer.
-// * Merge passes (Sec. 3.2, binary merging): every wave produces one
-//   4096-key output tile of one merge of two runs.  Its two half-waves find
-//   the co-ranks of the tile's first and last output (the merge-path split,
-//   exact whatever the duplicates), the A piece is loaded ascending and the B
-//   piece reversed into one bitonic tile, a half-cleaner network sorts it
-//   (register bits of the STRIDED layout, transpose, those of the BLOCKED
-//   layout) and the tile is stored coalesced.  Passes ping-pong between the
+// * Merge passes (Sec. 3.2, binary merging): every work-group produces 8192
+//   outputs of one merge of two runs, every wave 2048 of them.  Co-ranks (the
+//   merge-path split, exact whatever the duplicates) bound each tile's pieces,
+//   the A piece is loaded ascending and the B piece reversed into one bitonic
+//   tile, a half-cleaner network sorts it and the tile is stored coalesced.  Passes ping-pong between the
 //   output and temp so that the last one writes the output.
 // Keys only: equal keys are indistinguishable, so the order among them needs
 // no tie-break.
@@ -87,38 +85,6 @@ __device__ __forceinline__ void store_tile64(const Lines64 &t, uint64_t *__restr
     }
 }
 
-// Round J (1..6) of the tile sort: pairs of sorted runs of 2^(5+J) positions,
-// alternating in direction, become runs of 2^(6+J).  Position bits 5+J..6 are
-// register bits in STRIDED layout (direction: register bit J), bits 5..0 in
-// BLOCKED layout (direction: lane bit J, applied by complementing).
-template <int J>
-__device__ __forceinline__ void merge_round64(Lines64 &t, uint32_t *lds, uint32_t lane)
-{
-    to_strided(t, lds, lane);
-    half_clean_lines<(1 << (J - 1)), (J < 6 ? J : -1)>(t);
-    to_blocked(t, lds, lane);
-    if constexpr (J < 6)
-        flip(t, lane >> J);
-    half_clean_lines<kLine / 2, -1>(t);
-    if constexpr (J < 6)
-        flip(t, lane >> J);
-}
-
-// Sort a wave tile: on entry as loaded (read as BLOCKED: lane l's line), on
-// exit sorted in BLOCKED layout.
-__device__ __forceinline__ void sort_tile_blocked64(Lines64 &t, uint32_t *lds, uint32_t lane)
-{
-    flip(t, lane);  // lines: even lanes ascending, odd lanes descending
-    oe_sort_lines<0, kLine - 1>(t);
-    flip(t, lane);
-    merge_round64<1>(t, lds, lane);
-    merge_round64<2>(t, lds, lane);
-    merge_round64<3>(t, lds, lane);
-    merge_round64<4>(t, lds, lane);
-    merge_round64<5>(t, lds, lane);
-    merge_round64<6>(t, lds, lane);
-}
-
 constexpr int kGroupWaves64 = 4;  // group tiles of 16384 keys
 constexpr uint64_t kGroupMinN64 = 1ull << 19;
 
@@ -135,7 +101,7 @@ __global__ __launch_bounds__(kWave) void k_u64_block_sort(const uint64_t *__rest
     const uint32_t count = n - start < (uint64_t)kTile ? (uint32_t)(n - start) : (uint32_t)kTile;
     Lines64 t;
     load_tile64(t, in + start, count, lane);
-    sort_tile_blocked64(t, lds, lane);
+    sort_tile_wide(t, lds, lane);
     to_strided(t, lds, lane);
     store_tile64<NT>(t, out + start, count, lane);
 }
@@ -145,8 +111,8 @@ __global__ __launch_bounds__(kWave) void k_u64_block_sort(const uint64_t *__rest
 // the group rounds merge across the waves.  Every wave of a work-group reaches
 // the same barriers: waves whose sub-tile lies past the end hold padding only.
 template <bool NT>
-__global__ __launch_bounds__(kWave *kGroupWaves64) void k_u64_block_sort_group(const uint64_t *__restrict__ in,
-                                                                             uint64_t *__restrict__ out, uint64_t n)
+__global__ __launch_bounds__(kWave *kGroupWaves64) __attribute__((amdgpu_waves_per_eu(2))) void k_u64_block_sort_group(
+    const uint64_t *__restrict__ in, uint64_t *__restrict__ out, uint64_t n)
 {
     __shared__ __align__(16) uint32_t lds[kGroupWaves64 * kLdsWords];
     const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -159,67 +125,184 @@ __global__ __launch_bounds__(kWave *kGroupWaves64) void k_u64_block_sort_group(c
     Lines64 t;
     load_tile64(t, in + start, count, lane);  // count 0: padding only, nothing loaded
     uint32_t *own = lds + kLdsWords * wave;
-    flip(t, wave);
-    sort_tile_blocked64(t, own, lane);
-    flip(t, wave);
+    if (count != 0) {  // else padding only
+        flip(t, wave);
+        sort_tile_wide(t, own, lane);
+        flip(t, wave);
+    }
     group_rounds<kGroupWaves64, 7>(t, lds, lane, wave);
     to_strided(t, own, lane);
     store_tile64<NT>(t, out + start, count, lane);
 }
 
+// A merge tile holds 2048 keys, 32 per lane: the registers of four waves per
+// SIMD.  Four waves of a work-group take four consecutive tiles: one search over
+// the runs per 8192 keys, the inner ones inside the work-group's own pieces.  A
+// pass is bound by its chain of loads and by the lines its searches fetch: a
+// search of its own per tile fetched as much as the keys.  Measured at 12,000,001
+// keys, per pass under the profiler: 57 us with 4096 keys per wave or with 2048,
+// 44 so (4.3 TB/s); the sort 776 -> 634 us.
+constexpr int kMergeLine = 32;
+constexpr int kMergeKeys = kMergeLine * kWave;
+constexpr int kMergeWaves = 4;                   // tiles of a work-group
+constexpr int kMergeStride = 36;  // LDS words per 32 positions: 16-byte rows of 8 lanes cover the 32 banks
+constexpr int kMergeLdsWords = kMergeKeys / 32 * kMergeStride;
+
+__device__ __forceinline__ void cx64(uint64_t &a, uint64_t &b)
+{
+    const uint64_t x = a, y = b;
+    const bool lt = x < y;
+    a = lt ? x : y;
+    b = lt ? y : x;
+}
+
+// Half-cleaner steps at register distances D, D/2, ..., 1.
+template <int D>
+__device__ __forceinline__ void clean32(uint64_t (&x)[kMergeLine])
+{
+#pragma unroll
+    for (int r = 0; r < kMergeLine; ++r)
+        if ((r & D) == 0)
+            cx64(x[r], x[r + D]);
+    if constexpr (D > 1)
+        clean32<D / 2>(x);
+}
+
+// The word of both halves that `at` (0: low, 32: high) names.
+__device__ __forceinline__ uint32_t word_of(uint64_t x, int at) { return (uint32_t)(x >> at); }
+
+// Sorts a bitonic tile: on entry and exit position 64 r + lane in register r.
+// Position bits 10..6 are register bits; bit 5 (lane bit 5) meets through an
+// exchange of the half-waves of two registers, after which lane bit 5 holds
+// position bit 10 and register bit 4 position bit 5; bits 4..0 are register
+// bits once position 32 lane + r is in register r.
+__device__ __forceinline__ void merge_tile64(uint64_t (&x)[kMergeLine], uint32_t *lds, uint32_t lane)
+{
+    constexpr int H = kMergeLine / 2;
+    clean32<H>(x);
+#pragma unroll
+    for (int r = 0; r < H; ++r) {
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x[r], (uint32_t)x[r + H], false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x[r] >> 32), (uint32_t)(x[r + H] >> 32), false, false);
+        x[r] = ((uint64_t)hi[0] << 32) | lo[0];
+        x[r + H] = ((uint64_t)hi[1] << 32) | lo[1];
+        cx64(x[r], x[r + H]);
+    }
+    uint32_t *half = lds + kMergeStride * (32 * (lane >> 5)) + (lane & 31);    // rows of p bit 10
+    uint32_t *pairs = lds + kMergeStride * (lane >> 5) + (lane & 31);          // rows of p bit 5
+    uint32_t *row = static_cast<uint32_t *>(__builtin_assume_aligned(lds + kMergeStride * lane, 16));
+    uint32_t w[2][kMergeLine];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < kMergeLine; ++r)
+            half[kMergeStride * (2 * (r % H) + r / H)] = word_of(x[r], 32 * h);
+        wave_lds_fence();
+#pragma unroll
+        for (int r = 0; r < kMergeLine; ++r)
+            w[h][r] = row[r];
+        wave_lds_fence();
+    }
+#pragma unroll
+    for (int r = 0; r < kMergeLine; ++r)
+        x[r] = ((uint64_t)w[1][r] << 32) | w[0][r];
+    clean32<H>(x);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int r = 0; r < kMergeLine; ++r)
+            row[r] = word_of(x[r], 32 * h);
+        wave_lds_fence();
+#pragma unroll
+        for (int r = 0; r < kMergeLine; ++r)
+            w[h][r] = pairs[2 * kMergeStride * r];
+        wave_lds_fence();
+    }
+#pragma unroll
+    for (int r = 0; r < kMergeLine; ++r)
+        x[r] = ((uint64_t)w[1][r] << 32) | w[0][r];
+}
+
 // Output tile t of a binary pass over runs of `run` keys (a multiple of
 // 4096): runs 2s and 2s+1 merge into [2s run, min(2(s+1) run, n)).
 template <bool NT>
-__global__ __launch_bounds__(kWave) void k_u64_merge(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
-                                                     uint64_t n, uint64_t run)
+__global__ __launch_bounds__(kWave *kMergeWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_u64_merge(
+    const uint64_t *__restrict__ src, uint64_t *__restrict__ dst, uint64_t n, uint64_t run)
 {
-    __shared__ __align__(16) uint32_t lds[kLdsWords];
-    const uint32_t lane = threadIdx.x;
-    const uint64_t gstart = (uint64_t)blockIdx.x * kTile;
+    __shared__ __align__(16) uint32_t lds_all[kMergeWaves][kMergeLdsWords];
+    __shared__ uint32_t cut[kMergeWaves + 1];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    uint32_t *lds = lds_all[wave];
+    uint64_t gstart = (uint64_t)blockIdx.x * (kMergeWaves * kMergeKeys);
     if (gstart >= n)
         return;
     const uint64_t base = gstart / (2 * run) * (2 * run);
     const uint64_t rem = n - base;
     const uint32_t na = (uint32_t)(rem < run ? rem : run);
     const uint32_t nb = (uint32_t)(rem - na < run ? rem - na : run);
-    const uint32_t d0 = (uint32_t)(gstart - base);
-    const uint32_t count = na + nb - d0 < (uint32_t)kTile ? na + nb - d0 : (uint32_t)kTile;
+    const uint32_t g0 = (uint32_t)(gstart - base);
+    const uint32_t gcount = min(na + nb - g0, (uint32_t)(kMergeWaves * kMergeKeys));
     const uint64_t *A = src + base, *B = A + na;
-    // lanes 0..31: co-rank of the tile's first output, 32..63: of its end
-    const uint32_t d = lane < 32 ? d0 : d0 + count;
-    const uint32_t split = corank_halfwave(A, na, B, nb, d, lane);
-    const uint32_t a0 = __builtin_amdgcn_readlane(split, 0), a1 = __builtin_amdgcn_readlane(split, 32);
+    // the work-group's co-ranks (lanes 0..31: of its first output, 32..63: of its
+    // end), then those of its inner tiles, inside the pieces it is going to load
+    if (wave == 0) {
+        const uint32_t split = corank_halfwave(A, na, B, nb, lane < 32 ? g0 : g0 + gcount, lane);
+        if ((lane & 31) == 0)
+            cut[lane < 32 ? 0 : kMergeWaves] = split;
+    }
+    __syncthreads();
+    if (wave != 0) {
+        const uint32_t ga = cut[0], gpa = cut[kMergeWaves] - ga;
+        const uint32_t d = min(wave * kMergeKeys, gcount);
+        const uint32_t split = corank_halfwave(A + ga, gpa, B + (g0 - ga), gcount - gpa, d, lane);
+        if (lane == 0)
+            cut[wave] = ga + split;
+    }
+    __syncthreads();
+    if (wave * kMergeKeys >= gcount)
+        return;
+    const uint32_t a0 = uniform(cut[wave]), a1 = uniform(cut[wave + 1]);
+    const uint32_t d0 = g0 + wave * kMergeKeys, count = min(gcount - wave * kMergeKeys, (uint32_t)kMergeKeys);
+    gstart += wave * kMergeKeys;
     const uint32_t pa = a1 - a0, pb = count - pa;
-    // A piece ascending at [0, pa), B piece reversed at [4096 - pb, 4096):
+    // A piece ascending at [0, pa), B piece reversed at [2048 - pb, 2048):
     // position p reads pA[p] or pA[bend - p], the B piece lying dB keys after
     // the A piece; one 32-bit offset per register, every load issued before
     // any is used
     const uint64_t *pA = A + a0;
     const uint32_t dB = na - a0 + (d0 - a0);
-    const uint32_t bend = dB + (kTile - 1);
-    const uint32_t bstart = kTile - pb;
-    Lines64 t;
-    if (count == (uint32_t)kTile) {
+    const uint32_t bend = dB + (kMergeKeys - 1);
+    const uint32_t bstart = kMergeKeys - pb;
+    uint64_t x[kMergeLine];
+    if (count == (uint32_t)kMergeKeys) {
         // full tile: every position is in A or in B, no select after a load
 #pragma unroll
-        for (int r = 0; r < kLine; ++r) {
+        for (int r = 0; r < kMergeLine; ++r) {
             const uint32_t p = kWave * r + lane;
-            t.e[r] = ld64<NT>(pA + (p < pa ? p : bend - p));
+            x[r] = ld64<NT>(pA + (p < pa ? p : bend - p));
         }
     } else {
 #pragma unroll
-        for (int r = 0; r < kLine; ++r) {
+        for (int r = 0; r < kMergeLine; ++r) {
             const uint32_t p = kWave * r + lane;
             const bool in_a = p < pa, in_b = p >= bstart;
             const uint64_t k = ld64<NT>(pA + (in_a ? p : (in_b ? bend - p : 0u)));
-            t.e[r] = (in_a || in_b) ? k : kMaxKey64;
+            x[r] = (in_a || in_b) ? k : kMaxKey64;
         }
     }
-    half_clean_lines<kLine / 2, -1>(t);  // position bits 11..6
-    to_blocked(t, lds, lane);
-    half_clean_lines<kLine / 2, -1>(t);  // position bits 5..0
-    to_strided(t, lds, lane);
-    store_tile64<NT>(t, dst + gstart, count, lane);
+    merge_tile64(x, lds, lane);
+    uint64_t *out = dst + gstart;
+#pragma unroll
+    for (int r = 0; r < kMergeLine; ++r) {
+        const uint32_t p = kWave * r + lane;
+        if (p < count) {
+            if constexpr (NT)
+                __builtin_nontemporal_store(x[r], out + p);
+            else
+                out[p] = x[r];
+        }
+    }
 }
 
 uint64_t align256(uint64_t b) { return (b + 255) / 256 * 256; }
@@ -282,13 +365,15 @@ extern "C" bcf_status bcf_sort_u64(const uint64_t *keys_in, uint64_t *keys_out, 
     prof_end(scope);
     if (hipGetLastError() != hipSuccess)
         return BCF_ERR_DEVICE;
+    constexpr uint32_t kMergeGroup = kMergeWaves * kMergeKeys;
+    const uint32_t merge_groups = (uint32_t)((n + kMergeGroup - 1) / kMergeGroup);
     uint64_t run = run0;
     for (uint32_t j = 1; j <= passes; ++j, run *= 2) {
         scope = prof_begin("merge_u64", s, 16.0 * n);
         if (nt)
-            hipLaunchKernelGGL(k_u64_merge<true>, dim3(tiles), dim3(kWave), 0, s, buf(j - 1), buf(j), n, run);
+            hipLaunchKernelGGL(k_u64_merge<true>, dim3(merge_groups), dim3(kWave * kMergeWaves), 0, s, buf(j - 1), buf(j), n, run);
         else
-            hipLaunchKernelGGL(k_u64_merge<false>, dim3(tiles), dim3(kWave), 0, s, buf(j - 1), buf(j), n, run);
+            hipLaunchKernelGGL(k_u64_merge<false>, dim3(merge_groups), dim3(kWave * kMergeWaves), 0, s, buf(j - 1), buf(j), n, run);
         prof_end(scope);
         if (hipGetLastError() != hipSuccess)
             return BCF_ERR_DEVICE;
