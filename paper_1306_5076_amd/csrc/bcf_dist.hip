@@ -235,9 +235,13 @@ __global__ __launch_bounds__(kThreads) void k_dist_offsets(const uint64_t *__res
     __shared__ uint64_t part[kThreads];
     const uint32_t tid = threadIdx.x;
     const uint64_t a = min(np, (uint64_t)blockIdx.x * kScanBlock + (uint64_t)tid * kPer), e = min(np, a + kPer);
-    uint64_t sum = 0;
-    for (uint64_t i = a; i < e; ++i)
-        sum += len[i];
+    uint64_t sum = 0, own[kPer];  // all loads in flight at once: there are few work-groups
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k)
+        own[k] = a + k < e ? len[a + k] : 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k)
+        sum += own[k];
     part[tid] = sum;
     __syncthreads();
     for (uint32_t d = 1; d < kThreads; d *= 2) {  // inclusive Hillis-Steele scan
@@ -247,8 +251,11 @@ __global__ __launch_bounds__(kThreads) void k_dist_offsets(const uint64_t *__res
         __syncthreads();
     }
     uint64_t acc = boff[blockIdx.x] + part[tid] - sum;
-    for (uint64_t i = a; i < e; ++i) {
-        const uint64_t l = len[i];
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+        const uint64_t i = a + k, l = own[k];
+        if (i >= e)
+            break;
         pos[i] = acc;
         if (l) {  // tiles T with acc <= T * kOutTile < acc + l start in piece i
             for (uint64_t T = (acc + kOutTile - 1) / kOutTile; T < ntiles && T * kOutTile < acc + l; ++T)
@@ -267,16 +274,83 @@ __global__ __launch_bounds__(kThreads) void k_dist_offsets(const uint64_t *__res
 // (pos[p] <= o < pos[p + 1]), so every copy moves at least one key.  An
 // unsorted run can make the cuts non-monotone; then the walk stops early
 // (unspecified output) but never reads outside the input.
+// Tiles of more pieces than this let each key find its piece by itself.  A
+// work-group's walk is a chain of loads per piece, and the tile with the most
+// pieces ends last: 2^24 Zipf keys in 64 runs and 511 buckets 71 us, 29 so.  The
+// walk stays for tiles of a few pieces (its offsets are in the cache by then).
+constexpr uint32_t kWalkPieces = 8;
+
 __global__ __launch_bounds__(kThreads) void k_dist_scatter(const uint32_t *__restrict__ keys,
                                                            const uint64_t *__restrict__ pos,
                                                            const uint64_t *__restrict__ src,
                                                            const uint32_t *__restrict__ tile_first, uint64_t np,
                                                            uint64_t n, uint32_t *__restrict__ out)
 {
+    __shared__ uint32_t ends[kThreads];   // in the tile: one past each staged piece's last key
+    __shared__ uint64_t starts[kThreads];  // where the tile's first key of each staged piece comes from
+    __shared__ uint32_t counts[kThreads / 64];
+    const uint32_t tid = threadIdx.x;
     const uint64_t o0 = (uint64_t)blockIdx.x * kOutTile;
     const uint64_t o1 = min(n, o0 + kOutTile);
     uint64_t o = o0;
     uint64_t p = tile_first[blockIdx.x];
+    {
+        // the next kThreads pieces, staged at once
+        const uint64_t q = p + tid;
+        uint64_t pp = 0, pn = 0, from = 0;
+        bool in = false;
+        if (q < np) {
+            pp = pos[q];
+            pn = pos[q + 1];
+            from = src[q];
+            in = pp < o1;
+        }
+        const uint64_t lo = pp > o0 ? pp : o0, hi = pn < o1 ? pn : o1;
+        // (offsets that are not monotone, or reach past the input, come only from a
+        // run that was not sorted: the walk below stops there)
+        const bool fair = !in || (pp <= pn && (hi <= lo || (from + (lo - pp) <= n && hi - lo <= n - from - (lo - pp))));
+        ends[tid] = in ? (uint32_t)((hi > lo ? hi : lo) - o0) : kOutTile;
+        starts[tid] = from + (lo - pp);
+        const uint32_t here = (uint32_t)__popcll(__ballot(in));
+        if ((tid & 63) == 0)
+            counts[tid / 64] = here;
+        const bool bad = __syncthreads_or(!fair) != 0;
+        uint32_t pieces = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kThreads / 64; ++w)
+            pieces += counts[w];
+        // many short pieces: every key finds its own, all of a thread's loads in
+        // flight (a walk would take a chain of loads per piece)
+        if (!bad && pieces > kWalkPieces && pieces < kThreads && ends[pieces - 1] == o1 - o0) {
+            constexpr int kPer = kOutTile / kThreads;
+            uint32_t at[kPer];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k)
+                at[k] = 0;
+            for (uint32_t step = kThreads / 2; step > 0; step /= 2) {
+#pragma unroll
+                for (int k = 0; k < kPer; ++k) {
+                    const uint32_t j = tid + k * kThreads, t = at[k] + step;
+                    at[k] = t <= pieces && ends[t - 1] <= j ? t : at[k];  // pieces that end at or before key j
+                }
+            }
+            uint32_t v[kPer];
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const uint32_t j = tid + k * kThreads;
+                const bool key = o0 + j < o1;
+                const uint32_t b = at[k] ? ends[at[k] - 1] : 0;
+                v[k] = key ? keys[starts[key ? at[k] : 0] + (j - b)] : 0;
+            }
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const uint32_t j = tid + k * kThreads;
+                if (o0 + j < o1)
+                    out[o0 + j] = v[k];
+            }
+            return;
+        }
+    }
     while (o < o1 && p < np) {
         const uint64_t pp = pos[p], pn = pos[p + 1];
         if (pn <= o) {  // piece p ends before o
