@@ -2393,6 +2393,8 @@ static uint32_t persistent_groups(K kernel, uint64_t tiles)
 
 template <class K>
 static uint32_t resident_blocks(K kernel, int threads, uint64_t need);
+template <class K>
+static uint32_t spread_blocks(K kernel, int threads, uint64_t need);
 
 template <class Src>
 constexpr bool kHasDeviceCount = std::is_base_of_v<TableSortSrc, Src> || std::is_base_of_v<TableGroupSrc, Src>;
@@ -2417,11 +2419,12 @@ static hipError_t launch_sort(const Src &src, hipStream_t s, bool shear = false)
         const dim3 grid(persistent_groups(k_block_sort<P, Src, true>, src.ntiles)), block(kWave * kWavesPerGroup);
         hipLaunchKernelGGL((k_block_sort<P, Src, true>), grid, block, 0, s, src);
     } else if constexpr (P) {
-        const dim3 grid(persistent_groups(k_block_sort<true, Src>, src.ntiles)), block(kWave * kWavesPerGroup);
+        const uint64_t need = ((uint64_t)src.ntiles + kWavesPerGroup - 1) / kWavesPerGroup;
+        const dim3 grid(spread_blocks(k_block_sort<true, Src>, kWave * kWavesPerGroup, need)), block(kWave * kWavesPerGroup);
         hipLaunchKernelGGL((k_block_sort<true, Src>), grid, block, 0, s, src);
     } else {
         const uint32_t grid =
-            device_count(src) ? resident_blocks(k_block_sort_keys<Src>, kWave, src.ntiles) : src.ntiles;
+            device_count(src) ? spread_blocks(k_block_sort_keys<Src>, kWave, src.ntiles) : src.ntiles;
         hipLaunchKernelGGL(k_block_sort_keys<Src>, dim3(grid), dim3(kWave), 0, s, src);
     }
     return hipGetLastError();
@@ -2551,12 +2554,12 @@ static hipError_t launch_group_src(const Src &src, hipStream_t s)
     if (src.ngroups == 0)
         return hipSuccess;
     if constexpr (P) {
-        const uint32_t groups = resident_blocks(k_block_sort_group_pairs<NW, Src>, kWave * NW, src.ngroups);
+        const uint32_t groups = spread_blocks(k_block_sort_group_pairs<NW, Src>, kWave * NW, src.ngroups);
         hipLaunchKernelGGL((k_block_sort_group_pairs<NW, Src>), dim3(groups), dim3(kWave * NW), 0, s, src);
     } else {
         static_assert(NW == kKeyGroupWaves, "waves of a key group");
         const uint32_t grid =
-            device_count(src) ? resident_blocks(k_block_sort_group_keys<Src>, kWave * NW, src.ngroups) : src.ngroups;
+            device_count(src) ? spread_blocks(k_block_sort_group_keys<Src>, kWave * NW, src.ngroups) : src.ngroups;
         hipLaunchKernelGGL(k_block_sort_group_keys<Src>, dim3(grid), dim3(kWave * NW), 0, s, src);
     }
     return hipGetLastError();
@@ -2752,6 +2755,30 @@ static uint32_t resident_blocks(K kernel, int threads, uint64_t need)
     return (uint32_t)(need < most ? need : most);
 }
 
+// Work-groups of a launch that strides over `need` items: one per item, so
+// that the hardware hands the next item to whichever CU is free, up to some
+// times what is resident, which bounds the empty ones where the count is only
+// known on the device (at most one per segment).  A grid of only the resident
+// ones fixes each one's share ahead: 10,000 segments of up to 2^17 keys 1182
+// us, 1075 so.
+template <class K>
+static uint32_t spread_blocks(K kernel, int threads, uint64_t need)
+{
+    const uint64_t most = 32ull * resident_blocks(kernel, threads, ~0u);
+    return (uint32_t)(need < most ? need : most);
+}
+
+// Work-groups of the merges of a device-counted pass: one per item slot while
+// the slots are few (half of them, of CD cuts, usually hold nothing: a merge of
+// 60 runs of 16 M keys 201 -> 188 us), else the resident ones (with one per slot
+// 10,000 segments took 1108 us, with these 1055).
+template <class K>
+static uint32_t slot_blocks(K kernel, int threads, uint64_t need)
+{
+    const uint32_t resident = resident_blocks(kernel, threads, need);
+    return need <= 4ull * resident ? (uint32_t)need : resident;
+}
+
 hipError_t launch_merge4_table(Bufs kb, const Merge4Job *jobs, uint32_t njobs, uint32_t tasks, uint32_t *item_job,
                                uint32_t items, void *cuts, uint64_t keys, bool merge, hipStream_t s,
                                const uint32_t *counts_dev, Bufs vb)
@@ -2779,20 +2806,20 @@ hipError_t launch_merge4_table(Bufs kb, const Merge4Job *jobs, uint32_t njobs, u
     if (pairs) {
         if (nt) {
             const uint32_t grid =
-                dev_counts ? resident_blocks(k_merge4_table_pairs<true>, kWave * kMerge4Waves, items) : items;
+                dev_counts ? slot_blocks(k_merge4_table_pairs<true>, kWave * kMerge4Waves, items) : items;
             hipLaunchKernelGGL(k_merge4_table_pairs<true>, dim3(grid), block, 0, s, src);
         } else {
             const uint32_t grid =
-                dev_counts ? resident_blocks(k_merge4_table_pairs<false>, kWave * kMerge4Waves, items) : items;
+                dev_counts ? slot_blocks(k_merge4_table_pairs<false>, kWave * kMerge4Waves, items) : items;
             hipLaunchKernelGGL(k_merge4_table_pairs<false>, dim3(grid), block, 0, s, src);
         }
         return hipGetLastError();
     }
     if (nt) {
-        const uint32_t grid = dev_counts ? resident_blocks(k_merge4_table<true>, kWave * kMerge4Waves, items) : items;
+        const uint32_t grid = dev_counts ? slot_blocks(k_merge4_table<true>, kWave * kMerge4Waves, items) : items;
         hipLaunchKernelGGL(k_merge4_table<true>, dim3(grid), block, 0, s, src);
     } else {
-        const uint32_t grid = dev_counts ? resident_blocks(k_merge4_table<false>, kWave * kMerge4Waves, items) : items;
+        const uint32_t grid = dev_counts ? slot_blocks(k_merge4_table<false>, kWave * kMerge4Waves, items) : items;
         hipLaunchKernelGGL(k_merge4_table<false>, dim3(grid), block, 0, s, src);
     }
     return hipGetLastError();
