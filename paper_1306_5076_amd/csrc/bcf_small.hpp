@@ -8,119 +8,9 @@
 // Included by bcf_kernels.hip (it uses the key maps and samples defined there).
 #pragma once
 
+#include "bcf_tile16.hpp"
+
 namespace bcf {
-
-constexpr int kSmallWaves = 4;
-constexpr int kSmallThreads = kSmallWaves * kWave;
-constexpr int kSmallLine = kTile / kSmallThreads;  // 16 elements per lane
-static_assert(kSmallLine == 16, "the register networks below");
-
-// x of lane (lane ^ MASK), MASK below 64.  Within a row of 16 lanes by DPP
-// moves, within 32 lanes by the LDS crossbar (ds_swizzle, no LDS memory), else
-// by ds_bpermute.
-template <int MASK>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t x, uint32_t lane)
-{
-    if constexpr (MASK == 1)
-        return dpp_move<kDppXor1>(x);
-    else if constexpr (MASK == 2)
-        return dpp_move<kDppXor2>(x);
-    else if constexpr (MASK == 3)
-        return dpp_move<kDppXor3>(x);
-    else if constexpr (MASK == 4)
-        return dpp_move<kDppXor3>(dpp_move<kDppXor7>(x));
-    else if constexpr (MASK == 7)
-        return dpp_move<kDppXor7>(x);
-    else if constexpr (MASK == 8)
-        return dpp_move<0x128>(x);  // row_ror:8
-    else if constexpr (MASK == 15)
-        return dpp_move<0x140>(x);  // row_mirror
-    else if constexpr (MASK < 32)
-        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (MASK << 10) | 0x1f);
-    else
-        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane ^ MASK) * 4), (int)x);
-}
-template <int MASK>
-__device__ __forceinline__ double lane_xor(double x, uint32_t lane)
-{
-    const uint64_t b = bits_of(x);
-    const uint32_t hi = lane_xor<MASK>((uint32_t)(b >> 32), lane), lo = lane_xor<MASK>((uint32_t)b, lane);
-    return elem_of(((uint64_t)hi << 32) | lo);
-}
-
-// The smaller of x and y where `keep` is 0, the larger where it is ~0.
-__device__ __forceinline__ uint32_t keep_one(uint32_t x, uint32_t y, uint32_t keep) { return med3(x, y, keep); }
-__device__ __forceinline__ double keep_one(double x, double y, uint32_t keep)
-{
-    return ((x < y) != (keep != 0)) ? x : y;  // equal elements are padding, alike in every bit
-}
-
-// One stage against lane ^ MASK; with MIRROR against its mirrored register.
-template <int MASK, bool MIRROR, bool P>
-__device__ __forceinline__ void small_lane_clean(Lines<P> &t, uint32_t lane)
-{
-    constexpr int kTop = MASK & ~(MASK >> 1);  // highest bit: its holders keep the larger
-    const uint32_t keep = opaque((lane & kTop) ? ~0u : 0u);
-    auto &x = elems(t);
-    typename std::remove_reference<decltype(x[0])>::type y[kSmallLine];
-#pragma unroll
-    for (int r = 0; r < kSmallLine; ++r)
-        y[r] = lane_xor<MASK>(x[MIRROR ? kSmallLine - 1 - r : r], lane);
-#pragma unroll
-    for (int r = 0; r < kSmallLine; ++r)
-        x[r] = keep_one(x[r], y[r], keep);
-}
-
-// The stages on lane bits B .. 0 and on the registers that end every round.
-template <int B, bool P>
-__device__ __forceinline__ void small_lanes_down(Lines<P> &t, uint32_t lane)
-{
-    if constexpr (B >= 0) {
-        small_lane_clean<(1 << (B < 0 ? 0 : B)), false>(t, lane);
-        small_lanes_down<B - 1>(t, lane);
-    } else {
-        half_clean_lines<kSmallLine / 2, -1>(t);
-    }
-}
-
-// Round J (1..6): lanes l and l ^ (2^J - 1) hold mirrored places of two
-// ascending runs.
-template <int J, bool P>
-__device__ __forceinline__ void small_round(Lines<P> &t, uint32_t lane)
-{
-    small_lane_clean<(1 << J) - 1, true>(t, lane);
-    small_lanes_down<J - 2>(t, lane);
-}
-
-// The same stage against wave ^ mask, through LDS words [wave][register][lane].
-template <bool MIRROR, bool P>
-__device__ __forceinline__ void small_wave_clean(Lines<P> &t, uint32_t *buf, uint32_t wave, uint32_t mask, uint32_t lane)
-{
-    constexpr int N = kSmallLine;
-    const uint32_t other = wave ^ mask;
-    const uint32_t keep = wave > other ? ~0u : 0u;
-    uint32_t *w = buf + wave * N * kWave + lane;
-    const uint32_t *rd = buf + other * N * kWave + (MIRROR ? kWave - 1 - lane : lane);
-    auto &x = elems(t);
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-        if constexpr (P) {
-            w[r * kWave] = (uint32_t)(bits_of(x[r]) >> 32);
-            w[kTile + r * kWave] = (uint32_t)bits_of(x[r]);
-        } else {
-            w[r * kWave] = x[r];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-        const int q = (MIRROR ? N - 1 - r : r) * kWave;
-        if constexpr (P)
-            x[r] = keep_one(x[r], elem_of(((uint64_t)rd[q] << 32) | rd[kTile + q]), keep);
-        else
-            x[r] = keep_one(x[r], rd[q], keep);
-    }
-}
 
 typedef uint32_t Quad __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at any word
 
@@ -170,19 +60,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_tile_sort(Src src)
                 t.k[r] = k;
         }
     }
-    oe_sort_lines<0, N - 1>(t);
-    small_round<1>(t, lane);
-    small_round<2>(t, lane);
-    small_round<3>(t, lane);
-    small_round<4>(t, lane);
-    small_round<5>(t, lane);
-    small_round<6>(t, lane);
-    small_wave_clean<true>(t, lds[0], wave, 1, lane);
-    small_lanes_down<5>(t, lane);
-    small_wave_clean<true>(t, lds[1], wave, 3, lane);
-    // the first buffer again: every wave has read it before the barrier above
-    small_wave_clean<false>(t, lds[0], wave, 1, lane);
-    small_lanes_down<5>(t, lane);
+    small_sort(t, lds[0], lds[1], wave, lane);
     // samples: the first and last key of every 64-key block and of the tile
     const uint32_t p0 = N * tid;
     if (src.out_smp.f != nullptr && (tid / 4) * kLine < count) {

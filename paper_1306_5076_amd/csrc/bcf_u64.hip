@@ -26,6 +26,7 @@
 
 #include "bcf.h"
 #include "bcf_device.hpp"
+#include "bcf_tile16.hpp"
 
 namespace bcf {
 
@@ -88,22 +89,41 @@ __device__ __forceinline__ void store_tile64(const Lines64 &t, uint64_t *__restr
 constexpr int kGroupWaves64 = 4;  // group tiles of 16384 keys
 constexpr uint64_t kGroupMinN64 = 1ull << 19;
 
-// One 4096-key tile per wave, one wave per work-group.
-template <bool NT>
-__global__ __launch_bounds__(kWave) void k_u64_block_sort(const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
-                                                          uint64_t n)
+// One 4096-key tile per work-group of four waves, 16 keys per lane: sorts of at
+// most 2^19 keys leave the chip nearly empty, and one wave with 64 keys per lane
+// takes 53 us for its chain of instructions.
+__global__ __launch_bounds__(kSmallThreads) void k_u64_tile_sort(const uint64_t *__restrict__ in,
+                                                                 uint64_t *__restrict__ out, uint64_t n)
 {
-    __shared__ __align__(16) uint32_t lds[kLdsWords];
-    const uint32_t lane = threadIdx.x;
+    constexpr int N = kSmallLine;
+    __shared__ __align__(16) uint32_t lds[2][2 * kTile];
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const uint64_t start = (uint64_t)blockIdx.x * kTile;
     if (start >= n)
         return;
     const uint32_t count = n - start < (uint64_t)kTile ? (uint32_t)(n - start) : (uint32_t)kTile;
-    Lines64 t;
-    load_tile64(t, in + start, count, lane);
-    sort_tile_wide(t, lds, lane);
-    to_strided(t, lds, lane);
-    store_tile64<NT>(t, out + start, count, lane);
+    Lines64 t{};
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        const uint32_t p = kSmallThreads * r + tid;
+        const uint64_t k = in[start + (p < count ? p : count - 1)];  // clamped: a valid address
+        t.e[r] = p < count ? k : kMaxKey64;
+    }
+    small_sort(t, lds[0], lds[1], wave, lane);
+    // through LDS, so that consecutive lanes store consecutive keys: position p at
+    // word pair p ^ (p / 16 mod 16), which spreads a lane's 16 keys over the banks
+    uint64_t *stage = reinterpret_cast<uint64_t *>(lds[1]);
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+        stage[N * tid + (r ^ (tid & (N - 1)))] = t.e[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        const uint32_t p = kSmallThreads * r + tid;
+        if (p < count)
+            out[start + p] = stage[p ^ ((p / N) & (N - 1))];
+    }
 }
 
 // One group tile of kGroupWaves64 sub-tiles per work-group: each wave sorts
@@ -357,10 +377,8 @@ extern "C" bcf_status bcf_sort_u64(const uint64_t *keys_in, uint64_t *keys_out, 
             hipLaunchKernelGGL(k_u64_block_sort_group<true>, dim3(groups), block, 0, s, keys_in, buf(0), n);
         else
             hipLaunchKernelGGL(k_u64_block_sort_group<false>, dim3(groups), block, 0, s, keys_in, buf(0), n);
-    } else if (nt) {
-        hipLaunchKernelGGL(k_u64_block_sort<true>, dim3(tiles), dim3(kWave), 0, s, keys_in, buf(0), n);
     } else {
-        hipLaunchKernelGGL(k_u64_block_sort<false>, dim3(tiles), dim3(kWave), 0, s, keys_in, buf(0), n);
+        hipLaunchKernelGGL(k_u64_tile_sort, dim3(tiles), dim3(kSmallThreads), 0, s, keys_in, buf(0), n);
     }
     prof_end(scope);
     if (hipGetLastError() != hipSuccess)

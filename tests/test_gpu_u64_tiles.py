@@ -27,3 +27,19 @@ def test_u64_merge_tiles(n):
     for name, keys in orders.items():
         got = bcf.sort_u64(torch.from_numpy(keys).cuda()).cpu().numpy()
         assert np.array_equal(got, oracle.sort_u64(keys)), (name, n)
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 255, 1023, 1024, 1025, 2049, 4080, 4096 + 17, 8192])
+def test_u64_tile_of_four_waves(n):
+    import torch
+
+    import paper_1306_5076_amd as bcf
+
+    rng = np.random.default_rng(n)
+    for keys in (rng.integers(0, 1 << 64, n, dtype=np.uint64), rng.integers(0, 3, n, dtype=np.uint64) << np.uint64(62),
+                 np.arange(n, 0, -1, dtype=np.uint64) << np.uint64(30), np.full(n, ~np.uint64(0), dtype=np.uint64)):
+        want = oracle.sort_u64(keys)
+        t = torch.from_numpy(keys).cuda()
+        assert np.array_equal(bcf.sort_u64(t).cpu().numpy(), want), n
+        bcf.sort_u64(t, out=t)
+        assert np.array_equal(t.cpu().numpy(), want), n
