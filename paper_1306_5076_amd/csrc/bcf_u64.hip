@@ -2,23 +2,20 @@
 // 32-bit keys) on the same design as the 32-bit sort, with a key held in a
 // register pair and compared as one 64-bit integer.
 //
-// * Block sort (the paper's base case, Sec. 3.1, as the 32-bit wave tiles do
-//   it): a wave holds a 64 x 64 tile of keys, 64 per lane.  Each lane sorts
-//   its line with Batcher's odd-even merge sort, lines alternating direction,
-//   then six bitonic merge rounds turn the 64 lines into one sorted run of
-//   4096 keys.  Every compare-exchange is between two registers of one lane;
-//   the switches between the STRIDED and BLOCKED layouts go through LDS as
-//   two 32-bit halves, each with the conflict-free 68-word rows of the 32-bit
-//   tiles.  Above 2^19 keys four waves of a work-group then merge their
-//   sorted sub-tiles in two more rounds through the shared CROSS layout (the
-//   group tiles of the 32-bit sort), for runs of 16384 keys: two merge passes
-//   fewer.
+// * Block sort (the paper's base case, Sec. 3.1): up to 6 M keys, four waves sort a
+//   tile of 4096 keys with 16 keys per lane (the networks of the small 32-bit
+//   sorts).  Above, four waves sort 16384 keys: each lane sorts a line of 64
+//   with Batcher's odd-even merge sort, six merge rounds turn a wave's 64 lines
+//   into one run of 4096 keys, and two more rounds through the shared CROSS
+//   layout merge the waves' runs.  Layout changes go through LDS as two 32-bit
+//   halves, each with the conflict-free rows of the 32-bit tiles.
 // * Merge passes (Sec. 3.2, binary merging): every work-group produces 8192
 //   outputs of one merge of two runs, every wave 2048 of them.  Co-ranks (the
 //   merge-path split, exact whatever the duplicates) bound each tile's pieces,
 //   the A piece is loaded ascending and the B piece reversed into one bitonic
-//   tile, a half-cleaner network sorts it and the tile is stored coalesced.  Passes ping-pong between the
-//   output and temp so that the last one writes the output.
+//   tile, a half-cleaner network sorts it and the tile is stored coalesced.
+//   Passes ping-pong between the output and temp so that the last one writes
+//   the output.
 // Keys only: equal keys are indistinguishable, so the order among them needs
 // no tie-break.
 #include <hip/hip_runtime.h>
@@ -87,7 +84,10 @@ __device__ __forceinline__ void store_tile64(const Lines64 &t, uint64_t *__restr
 }
 
 constexpr int kGroupWaves64 = 4;  // group tiles of 16384 keys
-constexpr uint64_t kGroupMinN64 = 1ull << 19;
+// Sorts of more keys than this take group tiles.  Four-wave tiles and two more
+// merge passes against group tiles: 2^20 keys 144 / 206 us, 2^22 230 / 257, 6 M 318 /
+// 337, 2^23 405 / 397.
+constexpr uint64_t kGroupMinN64 = 6ull << 20;
 
 // One 4096-key tile per work-group of four waves, 16 keys per lane: sorts of at
 // most 2^19 keys leave the chip nearly empty, and one wave with 64 keys per lane
