@@ -137,9 +137,9 @@ bcf_status bcf_sort_u64(const uint64_t *keys_in, uint64_t *keys_out, uint64_t n,
                         uint64_t *temp_bytes, void *stream);
 
 /*
- * Merge k sorted runs into one sorted sequence (the paper's binary merging of
- * sorted sequences larger than on-chip memory, Sec. 3.2, applied pairwise in
- * ceil(log2 k) passes).  Stable: among equal keys, lower run index first, then
+ * Merge k sorted runs into one sorted sequence (the paper's merging of sorted
+ * sequences larger than on-chip memory, Sec. 3.2, four runs at a time in
+ * ceil(log4 k) passes, or pairwise under merge_fan_in 2).  Stable: among equal keys, lower run index first, then
  * earlier position.
  *   keys_in      device, run r occupies [run_offsets[r], run_offsets[r+1])
  *   vals_in      device values carried with the keys, or NULL for keys only

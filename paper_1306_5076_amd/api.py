@@ -295,8 +295,9 @@ def merge_runs(keys, run_offsets, vals=None, keys_out=None, vals_out=None, strea
     """Stable merge of the sorted runs [off[r], off[r+1]) of ``keys``.
 
     ``run_offsets`` holds k+1 offsets: a CUDA tensor (int64 / uint64) takes the
-    device-planned ``bcf_merge_runs`` (nothing read back while merging), a host
-    sequence ``bcf_merge_runs_host``.  Returns ``keys_out``, or
+    device-planned ``bcf_merge_runs`` (nothing read back: offsets that are not
+    nondecreasing from 0, or end past the keys, are found on the device and
+    nothing is written), a host sequence ``bcf_merge_runs_host``.  Returns ``keys_out``, or
     ``(keys_out, vals_out)`` when ``vals`` is given.
     """
     lib = load()
@@ -470,7 +471,9 @@ def segmented_sort(keys, seg_offsets, vals=None, keys_out=None, vals_out=None, s
     """Sort every segment [off[s], off[s+1]) of ``keys`` independently.
 
     With ``vals`` the sort is a stable key/value sort per segment and
-    ``(keys_out, vals_out)`` is returned; otherwise ``keys_out``.
+    ``(keys_out, vals_out)`` is returned; otherwise ``keys_out``.  Offsets on
+    the device are never read back: ones that are not nondecreasing from 0, or
+    end past the keys, are found there, and nothing is written.
     """
     lib = load()
     _check_tensor(keys, "keys")
