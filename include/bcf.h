@@ -172,6 +172,21 @@ bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, cons
 bcf_status bcf_merge_runs_temp(uint64_t n, uint32_t k, int pairs, uint64_t *temp_bytes);
 bcf_status bcf_segmented_sort_temp(uint64_t n, uint32_t nseg, int pairs, uint64_t *temp_bytes);
 
+/*
+ * bcf_merge_runs, and bcf_segmented_sort (pairs = 0) or
+ * bcf_segmented_sort_pairs (pairs != 0), on arrays of n keys each: offsets that
+ * end past n are invalid like those that end past the capacity, and nothing is
+ * written.  (The capacity is what the plan can do with the buffer: it lies
+ * above the keys that the buffer was sized for.)
+ * Without a query (temp must not be NULL): sized by the calls above.
+ */
+bcf_status bcf_merge_runs_within(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets,
+                                 uint32_t k, uint64_t n, uint32_t *keys_out, uint32_t *vals_out, void *temp,
+                                 uint64_t *temp_bytes, void *stream);
+bcf_status bcf_segmented_sort_within(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_out,
+                                     uint32_t *vals_out, const uint64_t *seg_offsets, uint32_t nseg, uint64_t n,
+                                     int pairs, void *temp, uint64_t *temp_bytes, void *stream);
+
 /* bcf_merge_runs with HOST offsets, planned on the host (the plan goes to the
  * device with one copy through pinned staging); empty runs are dropped from
  * the plan.  The temp size depends on the offsets, not only on their total. */

@@ -305,8 +305,7 @@ def merge_runs(keys, run_offsets, vals=None, keys_out=None, vals_out=None, strea
     n = keys.numel()
     doff = _device_offsets(run_offsets, keys.device)
     if doff is not None:
-        return _planned(lib.bcf_merge_runs, "bcf_merge_runs", keys, doff, vals, keys_out, vals_out, stream, workspace,
-                        merge=True)
+        return _planned("bcf_merge_runs", keys, doff, vals, keys_out, vals_out, stream, workspace, merge=True)
     off = _offsets(run_offsets, n)
     k = off.size - 1
     if vals is not None:
@@ -332,8 +331,9 @@ def merge_runs(keys, run_offsets, vals=None, keys_out=None, vals_out=None, strea
     return (keys_out, vals_out) if vals is not None else keys_out
 
 
-def _planned(fn, fname, keys, off, vals, keys_out, vals_out, stream, workspace, merge):
+def _planned(fname, keys, off, vals, keys_out, vals_out, stream, workspace, merge):
     """A call of a device-planned entry point (offsets in device memory)."""
+    lib = load()
     k = off.numel() - 1
     if vals is not None:
         _check_tensor(vals, "vals", keys.device)
@@ -342,23 +342,25 @@ def _planned(fn, fname, keys, off, vals, keys_out, vals_out, stream, workspace, 
     if vals is not None and vals_out is None:
         vals_out = torch.empty_like(vals)
     stream, sh = _stream(stream, keys.device)
+    # the keys that every array holds: offsets past them are found on the device
+    arrays = (keys, keys_out) if vals is None or not vals.numel() else (keys, keys_out, vals, vals_out)
+    n = min(t.numel() for t in arrays)
     # sized by the keys there are: asking the entry point would read the last
     # offset back and wait for the stream on every call
     need = ctypes.c_uint64(0)
-    size = load().bcf_merge_runs_temp if merge else load().bcf_segmented_sort_temp
-    check(fname, size(min(keys.numel(), 0xFFFFFFFF), max(k, 0), int(vals is not None), ctypes.byref(need)))
+    size = lib.bcf_merge_runs_temp if merge else lib.bcf_segmented_sort_temp
+    check(fname, size(min(n, 0xFFFFFFFF), k, int(vals is not None), ctypes.byref(need)))
     temp, _ = _temp(workspace, need.value, keys.device, stream)
-    tb = need  # the capacity follows from it: a workspace may be larger than these keys
+    tb = need  # passes are planned for as many keys: a workspace may be larger than these keys
     if keys.numel() and k:
         tp = _ptr(temp) or ctypes.c_void_p(1)
         if merge:
-            check(fname, fn(_ptr(keys), _ptr(vals), _ptr(off), k, _ptr(keys_out), _ptr(vals_out), tp, ctypes.byref(tb),
-                            sh))
-        elif vals is None:
-            check(fname, fn(_ptr(keys), _ptr(keys_out), _ptr(off), k, tp, ctypes.byref(tb), sh))
+            check(fname, lib.bcf_merge_runs_within(_ptr(keys), _ptr(vals), _ptr(off), k, n, _ptr(keys_out),
+                                                   _ptr(vals_out), tp, ctypes.byref(tb), sh))
         else:
-            check(fname, fn(_ptr(keys), _ptr(vals), _ptr(keys_out), _ptr(vals_out), _ptr(off), k, tp,
-                            ctypes.byref(tb), sh))
+            check(fname, lib.bcf_segmented_sort_within(_ptr(keys), _ptr(vals), _ptr(keys_out), _ptr(vals_out),
+                                                       _ptr(off), k, n, int(vals is not None), tp, ctypes.byref(tb),
+                                                       sh))
     return (keys_out, vals_out) if vals is not None else keys_out
 
 
@@ -482,10 +484,9 @@ def segmented_sort(keys, seg_offsets, vals=None, keys_out=None, vals_out=None, s
     doff = _device_offsets(seg_offsets, keys.device)
     if doff is not None:
         if vals is None:
-            return _planned(lib.bcf_segmented_sort, "bcf_segmented_sort", keys, doff, None, keys_out, None, stream,
-                            workspace, merge=False)
-        return _planned(lib.bcf_segmented_sort_pairs, "bcf_segmented_sort_pairs", keys, doff, vals, keys_out,
-                        vals_out, stream, workspace, merge=False)
+            return _planned("bcf_segmented_sort", keys, doff, None, keys_out, None, stream, workspace, merge=False)
+        return _planned("bcf_segmented_sort_pairs", keys, doff, vals, keys_out, vals_out, stream, workspace,
+                        merge=False)
     off = _offsets(seg_offsets, n)
     nseg = off.size - 1
     keys_out = torch.empty_like(keys) if keys_out is None else keys_out

@@ -101,7 +101,7 @@ struct PlanArgs {
     uint32_t PM;         // merge passes planned
     uint32_t four;       // fan-in 4 steps (PM4 passes, PM = 0) or binary ones (PM passes, PM4 = 0)
     uint32_t PM4;        // at most kMaxPlan4Passes
-    uint64_t cap;        // the most keys the temp buffer holds
+    uint64_t cap;        // the most keys: what the temp buffer holds, or the arrays where they hold less
     uint32_t *status;    // 0: plan valid; 1: offsets invalid or past the capacity
     // block-sort tiles (segments): counts per group, prefix, lists, totals
     uint32_t *bw, *bg;
@@ -686,9 +686,10 @@ uint64_t plan_capacity(const PlanSpec &sp, uint64_t bytes)
 bcf_status dev(hipError_t e) { return e == hipSuccess ? BCF_OK : BCF_ERR_DEVICE; }
 
 // Enqueue the planner kernels and the sort / merge kernels of a plan.  keys
-// (and values) in kb / vb; temp holds the layout for capacity cap.
+// (and values) in kb / vb; temp holds the layout for capacity cap, the arrays
+// `limit` keys: offsets that end past either are invalid.
 bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bufs vb, char *temp, uint64_t cap,
-                        hipStream_t s)
+                        uint64_t limit, hipStream_t s)
 {
     const PlanBounds b = plan_bounds(sp, cap);
     const PlanLayout L = plan_layout(sp, b, cap);
@@ -715,7 +716,7 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
     a.PM = PM;
     a.four = sp.four ? 1 : 0;
     a.PM4 = P4;
-    a.cap = cap;
+    a.cap = std::min(cap, limit);
     a.status = reinterpret_cast<uint32_t *>(temp + L.status);
     a.bw = reinterpret_cast<uint32_t *>(temp + L.bw);
     a.bg = reinterpret_cast<uint32_t *>(temp + L.bg);
@@ -846,10 +847,14 @@ Bufs val_bufs(const uint32_t *in, uint32_t *out, char *temp, uint64_t cap)
 }
 
 // A planned call: query (temp == NULL: the total is read from the device) or
-// run with the capacity the temp buffer holds.
+// run with the capacity the temp buffer holds, on arrays of `limit` keys.  The
+// capacity alone does not keep a call inside its arrays: it is what the plan
+// at hand can do with the buffer, above the keys the buffer was sized for
+// (sizes are rounded up, and those of merges reserve what either fan-in and an
+// extra copy pass need: 16,000,003 keys in 60 runs, capacity 16,033,536).
 bcf_status planned_call(const PlanSpec &worst, const PlanSpec &actual, const uint64_t *off_dev, const uint32_t *kin,
-                        const uint32_t *vin, uint32_t *kout, uint32_t *vout, void *temp, uint64_t *temp_bytes,
-                        hipStream_t s)
+                        const uint32_t *vin, uint32_t *kout, uint32_t *vout, uint64_t limit, void *temp,
+                        uint64_t *temp_bytes, hipStream_t s)
 {
     if (!temp) {
         uint64_t n = 0;
@@ -865,7 +870,7 @@ bcf_status planned_call(const PlanSpec &worst, const PlanSpec &actual, const uin
     char *tb = static_cast<char *>(temp);
     const Bufs kb = key_bufs(kin, kout, tb);
     const Bufs vb = actual.pairs ? val_bufs(vin, vout, tb, cap) : Bufs{nullptr, nullptr, nullptr};
-    return plan_and_run(actual, off_dev, kb, vb, tb, cap, s);
+    return plan_and_run(actual, off_dev, kb, vb, tb, cap, limit, s);
 }
 
 uint64_t seg_group_min(bool pairs, uint64_t knob) { return knob ? knob : group_run_keys(pairs) / 2; }
@@ -892,7 +897,8 @@ PlanSpec segments_spec(bool pairs, uint32_t nseg)
 }
 
 bcf_status segmented_device(bool pairs, const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
-                            const uint64_t *off, uint32_t nseg, void *temp, uint64_t *temp_bytes, hipStream_t s)
+                            const uint64_t *off, uint32_t nseg, uint64_t limit, void *temp, uint64_t *temp_bytes,
+                            hipStream_t s)
 {
     if (!temp_bytes)
         return BCF_ERR_INVALID;
@@ -904,7 +910,7 @@ bcf_status segmented_device(bool pairs, const uint32_t *kin, const uint32_t *vin
     if (!off)
         return BCF_ERR_INVALID;
     const PlanSpec sp = segments_spec(pairs, nseg);
-    return planned_call(sp, sp, off, kin, vin, kout, vout, temp, temp_bytes, s);
+    return planned_call(sp, sp, off, kin, vin, kout, vout, limit, temp, temp_bytes, s);
 }
 
 PlanSpec runs_spec(bool pairs, uint32_t k)
@@ -929,18 +935,10 @@ PlanSpec reserved(PlanSpec sp)
     return sp;
 }
 
-}  // namespace
-
-}  // namespace bcf
-
-using namespace bcf;
-
-extern "C" {
-
-bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets, uint32_t k,
-                          uint32_t *keys_out, uint32_t *vals_out, void *temp, uint64_t *temp_bytes, void *stream)
+bcf_status merge_runs_device(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets, uint32_t k,
+                             uint32_t *keys_out, uint32_t *vals_out, uint64_t limit, void *temp, uint64_t *temp_bytes,
+                             hipStream_t s)
 {
-    hipStream_t s = static_cast<hipStream_t>(stream);
     if (!temp_bytes)
         return BCF_ERR_INVALID;
     if (k == 0) {
@@ -967,6 +965,8 @@ bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, cons
         const uint64_t cap = plan_capacity(sp, *temp_bytes);
         if (plan_need(sp, cap) > *temp_bytes || n > cap)
             return BCF_ERR_TEMP_TOO_SMALL;
+        if (n > limit)
+            return BCF_OK;  // as the device check finds it: nothing is written
         const PlanLayout L = plan_layout(sp, plan_bounds(sp, cap), cap);
         uint32_t *flag_d = reinterpret_cast<uint32_t *>(static_cast<char *>(temp) + L.status + 12);
         uint32_t flag = 0;
@@ -979,7 +979,32 @@ bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, cons
         if (flag)
             return BCF_ERR_UNSORTED_RUN;
     }
-    return planned_call(worst, sp, run_offsets, keys_in, vals_in, keys_out, vals_out, temp, temp_bytes, s);
+    return planned_call(worst, sp, run_offsets, keys_in, vals_in, keys_out, vals_out, limit, temp, temp_bytes, s);
+}
+
+}  // namespace
+
+}  // namespace bcf
+
+using namespace bcf;
+
+extern "C" {
+
+bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets, uint32_t k,
+                          uint32_t *keys_out, uint32_t *vals_out, void *temp, uint64_t *temp_bytes, void *stream)
+{
+    return merge_runs_device(keys_in, vals_in, run_offsets, k, keys_out, vals_out, kMaxKeys, temp, temp_bytes,
+                             static_cast<hipStream_t>(stream));
+}
+
+bcf_status bcf_merge_runs_within(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets,
+                                 uint32_t k, uint64_t n, uint32_t *keys_out, uint32_t *vals_out, void *temp,
+                                 uint64_t *temp_bytes, void *stream)
+{
+    if (!temp)
+        return BCF_ERR_INVALID;
+    return merge_runs_device(keys_in, vals_in, run_offsets, k, keys_out, vals_out, n, temp, temp_bytes,
+                             static_cast<hipStream_t>(stream));
 }
 
 bcf_status bcf_merge_runs_temp(uint64_t n, uint32_t k, int pairs, uint64_t *temp_bytes)
@@ -1001,16 +1026,26 @@ bcf_status bcf_segmented_sort_temp(uint64_t n, uint32_t nseg, int pairs, uint64_
 bcf_status bcf_segmented_sort(const uint32_t *keys_in, uint32_t *keys_out, const uint64_t *seg_offsets, uint32_t nseg,
                               void *temp, uint64_t *temp_bytes, void *stream)
 {
-    return segmented_device(false, keys_in, nullptr, keys_out, nullptr, seg_offsets, nseg, temp, temp_bytes,
-                            static_cast<hipStream_t>(stream));
+    return segmented_device(false, keys_in, nullptr, keys_out, nullptr, seg_offsets, nseg, kMaxKeys, temp,
+                            temp_bytes, static_cast<hipStream_t>(stream));
 }
 
 bcf_status bcf_segmented_sort_pairs(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_out,
                                     uint32_t *vals_out, const uint64_t *seg_offsets, uint32_t nseg, void *temp,
                                     uint64_t *temp_bytes, void *stream)
 {
-    return segmented_device(true, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, temp, temp_bytes,
-                            static_cast<hipStream_t>(stream));
+    return segmented_device(true, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, kMaxKeys, temp,
+                            temp_bytes, static_cast<hipStream_t>(stream));
+}
+
+bcf_status bcf_segmented_sort_within(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_out,
+                                     uint32_t *vals_out, const uint64_t *seg_offsets, uint32_t nseg, uint64_t n,
+                                     int pairs, void *temp, uint64_t *temp_bytes, void *stream)
+{
+    if (!temp)
+        return BCF_ERR_INVALID;
+    return segmented_device(pairs != 0, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, n, temp,
+                            temp_bytes, static_cast<hipStream_t>(stream));
 }
 
 bcf_status bcf_sort_u32_pb(const uint32_t *keys_in, uint32_t *keys_out, uint64_t n, uint32_t P, uint32_t run_keys,
@@ -1071,7 +1106,7 @@ bcf_status bcf_sort_u32_pb(const uint32_t *keys_in, uint32_t *keys_out, uint64_t
     BCF_PLAN_TRY(bcf_distribute_runs(keys_out, seg.data(), s, P, P, pivot_buckets, dist, pieces, nullptr, scr, &sb,
                                      st));
     return plan_and_run(sp, pieces, key_bufs(dist, keys_out, static_cast<char *>(scr)), Bufs{nullptr, nullptr, nullptr},
-                        static_cast<char *>(scr), n, st);
+                        static_cast<char *>(scr), n, n, st);
 }
 
 }  // extern "C"
