@@ -178,14 +178,18 @@ bcf_status bcf_segmented_sort_temp(uint64_t n, uint32_t nseg, int pairs, uint64_
  * end past n are invalid like those that end past the capacity, and nothing is
  * written.  (The capacity is what the plan can do with the buffer: it lies
  * above the keys that the buffer was sized for.)
+ * total (host, or NULL) takes the last offset, which is refused above 2^32 - 1
+ * (BCF_ERR_INVALID; nothing is written): with it the call waits until its
+ * offsets have been read, behind what the stream holds already, but not for the
+ * rest of its launches.  In a stream capture it is left as it is.
  * Without a query (temp must not be NULL): sized by the calls above.
  */
 bcf_status bcf_merge_runs_within(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets,
-                                 uint32_t k, uint64_t n, uint32_t *keys_out, uint32_t *vals_out, void *temp,
-                                 uint64_t *temp_bytes, void *stream);
+                                 uint32_t k, uint64_t n, uint32_t *keys_out, uint32_t *vals_out, uint64_t *total,
+                                 void *temp, uint64_t *temp_bytes, void *stream);
 bcf_status bcf_segmented_sort_within(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_out,
                                      uint32_t *vals_out, const uint64_t *seg_offsets, uint32_t nseg, uint64_t n,
-                                     int pairs, void *temp, uint64_t *temp_bytes, void *stream);
+                                     int pairs, uint64_t *total, void *temp, uint64_t *temp_bytes, void *stream);
 
 /* bcf_merge_runs with HOST offsets, planned on the host (the plan goes to the
  * device with one copy through pinned staging); empty runs are dropped from

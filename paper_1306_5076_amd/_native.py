@@ -137,8 +137,8 @@ def load(path: str = LIB_PATH):
     lib.bcf_segmented_execute.argtypes = [vp, vp, vp, vp, u64p, u32, vp, u64p, vp]
     lib.bcf_merge_runs_temp.argtypes = [u64, u32, ctypes.c_int, u64p]
     lib.bcf_segmented_sort_temp.argtypes = [u64, u32, ctypes.c_int, u64p]
-    lib.bcf_merge_runs_within.argtypes = [vp, vp, vp, u32, u64, vp, vp, vp, u64p, vp]
-    lib.bcf_segmented_sort_within.argtypes = [vp, vp, vp, vp, vp, u32, u64, ctypes.c_int, vp, u64p, vp]
+    lib.bcf_merge_runs_within.argtypes = [vp, vp, vp, u32, u64, vp, vp, u64p, vp, u64p, vp]
+    lib.bcf_segmented_sort_within.argtypes = [vp, vp, vp, vp, vp, u32, u64, ctypes.c_int, u64p, vp, u64p, vp]
     for f in ("bcf_sort_u32", "bcf_sort_pairs_u32", "bcf_merge_runs", "bcf_merge_runs_host", "bcf_distribute_runs",
               "bcf_merge_runs_temp", "bcf_segmented_sort_temp", "bcf_merge_runs_within", "bcf_segmented_sort_within",
               "bcf_merge_run_groups", "bcf_sort_u32_pb", "bcf_segmented_sort", "bcf_segmented_sort_pairs",

@@ -9,6 +9,7 @@ comes from torch's caching allocator through :class:`Workspace`.
 from __future__ import annotations
 
 import ctypes
+import warnings
 
 import numpy as np
 import torch
@@ -54,6 +55,14 @@ def _stream(stream, device):
     if stream is None:
         stream = torch.cuda.current_stream(device)
     return stream, ctypes.c_void_p(stream.cuda_stream)
+
+
+def _capturing(stream):
+    """Whether the stream is being captured into a graph."""
+    if stream == torch.cuda.current_stream():
+        return torch.cuda.is_current_stream_capturing()
+    with torch.cuda.stream(stream):
+        return torch.cuda.is_current_stream_capturing()
 
 
 def _check_tensor(t, name, device=None):
@@ -107,6 +116,10 @@ class Workspace:
         if stream is not None and stream != torch.cuda.current_stream(device):
             self.buf.record_stream(stream)
         return self.buf
+
+    def holds(self, nbytes: int, device) -> bool:
+        """Whether get() would return the buffer there is."""
+        return nbytes == 0 or (self.buf is not None and self.buf.numel() >= nbytes and self.buf.device == device)
 
 
 def _temp(ws, nbytes, device, stream):
@@ -295,10 +308,15 @@ def merge_runs(keys, run_offsets, vals=None, keys_out=None, vals_out=None, strea
     """Stable merge of the sorted runs [off[r], off[r+1]) of ``keys``.
 
     ``run_offsets`` holds k+1 offsets: a CUDA tensor (int64 / uint64) takes the
-    device-planned ``bcf_merge_runs`` (nothing read back: offsets that are not
-    nondecreasing from 0, or end past the keys, are found on the device and
-    nothing is written), a host sequence ``bcf_merge_runs_host``.  Returns ``keys_out``, or
-    ``(keys_out, vals_out)`` when ``vals`` is given.
+    device-planned ``bcf_merge_runs``, a host sequence ``bcf_merge_runs_host``.
+    Returns ``keys_out``, or ``(keys_out, vals_out)`` when ``vals`` is given.
+
+    With offsets on the device the call waits until they have been read, for a
+    last offset above 2^32 - 1 raises; ones that are not nondecreasing from 0, or
+    end past the keys (a warning says so), are found there, and nothing is
+    written.  A workspace that holds temp for all of ``keys`` is used as it is;
+    without one the temp follows the last offset, which is read back first.  In
+    a graph capture nothing is read back, and temp is sized by the keys.
     """
     lib = load()
     _check_tensor(keys, "keys")
@@ -345,22 +363,42 @@ def _planned(fname, keys, off, vals, keys_out, vals_out, stream, workspace, merg
     # the keys that every array holds: offsets past them are found on the device
     arrays = (keys, keys_out) if vals is None or not vals.numel() else (keys, keys_out, vals, vals_out)
     n = min(t.numel() for t in arrays)
-    # sized by the keys there are: asking the entry point would read the last
-    # offset back and wait for the stream on every call
+    pairs = int(vals is not None)
     need = ctypes.c_uint64(0)
     size = lib.bcf_merge_runs_temp if merge else lib.bcf_segmented_sort_temp
-    check(fname, size(min(n, 0xFFFFFFFF), k, int(vals is not None), ctypes.byref(need)))
+    check(fname, size(min(n, 0xFFFFFFFF), k, pairs, ctypes.byref(need)))
+    capturing = _capturing(stream)
+    if not capturing and not (workspace is not None and workspace.holds(need.value, keys.device)):
+        # temp for the keys that the offsets cover, which may be few of those
+        # there are: the query reads the last offset back and waits for the
+        # stream.  A workspace that holds temp for all the keys needs no query.
+        exact = ctypes.c_uint64(0)
+        vdummy = ctypes.c_void_p(1) if pairs else None
+        if merge:
+            check(fname, lib.bcf_merge_runs(None, vdummy, _ptr(off), k, None, None, None, ctypes.byref(exact), sh))
+        elif pairs:
+            check(fname, lib.bcf_segmented_sort_pairs(None, None, None, None, _ptr(off), k, None, ctypes.byref(exact),
+                                                      sh))
+        else:
+            check(fname, lib.bcf_segmented_sort(None, None, _ptr(off), k, None, ctypes.byref(exact), sh))
+        need = min(need, exact, key=lambda x: x.value)
     temp, _ = _temp(workspace, need.value, keys.device, stream)
     tb = need  # passes are planned for as many keys: a workspace may be larger than these keys
     if keys.numel() and k:
         tp = _ptr(temp) or ctypes.c_void_p(1)
+        # the last offset: waits for the first launch of the call, and refuses
+        # totals above 2^32 - 1 (in a capture nothing can be waited for)
+        total = ctypes.c_uint64(0)
+        report = None if capturing else ctypes.byref(total)
         if merge:
             check(fname, lib.bcf_merge_runs_within(_ptr(keys), _ptr(vals), _ptr(off), k, n, _ptr(keys_out),
-                                                   _ptr(vals_out), tp, ctypes.byref(tb), sh))
+                                                   _ptr(vals_out), report, tp, ctypes.byref(tb), sh))
         else:
             check(fname, lib.bcf_segmented_sort_within(_ptr(keys), _ptr(vals), _ptr(keys_out), _ptr(vals_out),
-                                                       _ptr(off), k, n, int(vals is not None), tp, ctypes.byref(tb),
-                                                       sh))
+                                                       _ptr(off), k, n, pairs, report, tp, ctypes.byref(tb), sh))
+        if total.value > n:
+            warnings.warn(f"{fname}: the offsets end at {total.value}, past the {n} keys: nothing was written",
+                          RuntimeWarning, stacklevel=3)
     return (keys_out, vals_out) if vals is not None else keys_out
 
 
@@ -474,8 +512,7 @@ def segmented_sort(keys, seg_offsets, vals=None, keys_out=None, vals_out=None, s
 
     With ``vals`` the sort is a stable key/value sort per segment and
     ``(keys_out, vals_out)`` is returned; otherwise ``keys_out``.  Offsets on
-    the device are never read back: ones that are not nondecreasing from 0, or
-    end past the keys, are found there, and nothing is written.
+    the device are taken as by :func:`merge_runs`.
     """
     lib = load()
     _check_tensor(keys, "keys")

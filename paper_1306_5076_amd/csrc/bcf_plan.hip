@@ -28,6 +28,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "bcf.h"
@@ -102,6 +103,7 @@ struct PlanArgs {
     uint32_t four;       // fan-in 4 steps (PM4 passes, PM = 0) or binary ones (PM passes, PM4 = 0)
     uint32_t PM4;        // at most kMaxPlan4Passes
     uint64_t cap;        // the most keys: what the temp buffer holds, or the arrays where they hold less
+    uint64_t *total;     // host word for the last offset, or nullptr
     uint32_t *status;    // 0: plan valid; 1: offsets invalid or past the capacity
     // block-sort tiles (segments): counts per group, prefix, lists, totals
     uint32_t *bw, *bg;
@@ -227,11 +229,19 @@ __global__ void k_plan_zero(PlanArgs a)
         a.tcount[j] = 0;
 }
 
+__device__ void report_total(const PlanArgs &a, uint32_t noff)
+{
+    if (a.total)
+        __hip_atomic_store(a.total, a.off[noff - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Validity of the offsets: off[0] == 0, nondecreasing, total within the
 // capacity.  One thread per offset pair; any failure sets the status word.
 __global__ __launch_bounds__(kPlanBlock) void k_plan_check(PlanArgs a, uint32_t noff)
 {
     const uint32_t i = blockIdx.x * kPlanBlock + threadIdx.x;
+    if (i == 0)
+        report_total(a, noff);
     if (i == 0 && (a.off[0] != 0 || a.off[noff - 1] > a.cap))
         *a.status = 1;
     if (i + 1 < noff && a.off[i + 1] < a.off[i])
@@ -253,6 +263,7 @@ __global__ __launch_bounds__(kScanBlock) void k_plan_begin(PlanArgs a, uint32_t 
     }
     const int any = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
+        report_total(a, noff);
         *a.status = any ? 1 : 0;
         *a.wcount = 0;
         *a.gcount = 0;
@@ -685,11 +696,114 @@ uint64_t plan_capacity(const PlanSpec &sp, uint64_t bytes)
 
 bcf_status dev(hipError_t e) { return e == hipSuccess ? BCF_OK : BCF_ERR_DEVICE; }
 
+// Words of pinned host memory that a planner launch writes the last offset to,
+// each with the event recorded behind that launch.  A call holds one until the
+// event has passed; kTotalSlots are kept, which calls in flight on more threads
+// than that go beyond.
+struct TotalSlot {
+    uint64_t *word = nullptr;
+    hipEvent_t done = nullptr;
+    int dev = -1;
+};
+constexpr int kTotalSlots = 16;
+std::mutex g_total_mu;
+TotalSlot g_total[kTotalSlots];
+
+// The last offset of a call, which the host waits for after its launches: the
+// wait is for the planner's first launch, so that the rest of the call runs on
+// behind it.  Not reported in a stream capture (and without `out`).
+class TotalReport {
+public:
+    TotalReport(uint64_t *out, hipStream_t s) : out_(out)
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (!out || hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+            out_ = nullptr;
+            return;
+        }
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess)
+            dev = 0;
+        {
+            const std::lock_guard<std::mutex> hold(g_total_mu);
+            for (TotalSlot &f : g_total)
+                if (f.word && f.dev == dev) {
+                    slot_ = f;
+                    f = TotalSlot{};
+                    return;
+                }
+        }
+        // an allocation must not end the captures of other streams
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        void *w = nullptr;
+        if (hipHostMalloc(&w, sizeof(uint64_t), hipHostMallocDefault) == hipSuccess) {
+            slot_.word = static_cast<uint64_t *>(w);
+            slot_.dev = dev;
+            if (hipEventCreateWithFlags(&slot_.done, hipEventDisableTiming) != hipSuccess)
+                drop();
+        }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    TotalReport(const TotalReport &) = delete;
+    TotalReport &operator=(const TotalReport &) = delete;
+    ~TotalReport()
+    {
+        if (!slot_.word)
+            return;
+        if (recorded_)
+            (void)hipEventSynchronize(slot_.done);
+        const std::lock_guard<std::mutex> hold(g_total_mu);
+        for (TotalSlot &f : g_total)
+            if (!f.word) {
+                f = slot_;
+                return;
+            }
+        drop();
+    }
+    uint64_t *word() const { return slot_.word; }
+    bool failed() const { return out_ && !slot_.word; }
+    // After the launch that writes the word.
+    bcf_status record(hipStream_t s)
+    {
+        if (!out_)
+            return BCF_OK;
+        recorded_ = true;
+        if (hipEventRecord(slot_.done, s) == hipSuccess)
+            return BCF_OK;
+        (void)hipStreamSynchronize(s);  // the word goes back to the pool
+        return BCF_ERR_DEVICE;
+    }
+    // After the call's launches: the total, refused when no call takes it.
+    bcf_status wait()
+    {
+        if (!out_)
+            return BCF_OK;
+        if (hipEventSynchronize(slot_.done) != hipSuccess)
+            return BCF_ERR_DEVICE;
+        *out_ = __atomic_load_n(slot_.word, __ATOMIC_RELAXED);
+        return *out_ > kMaxKeys ? BCF_ERR_INVALID : BCF_OK;
+    }
+
+private:
+    void drop()
+    {
+        if (slot_.done)
+            (void)hipEventDestroy(slot_.done);
+        (void)hipHostFree(slot_.word);
+        slot_ = TotalSlot{};
+    }
+    uint64_t *out_;
+    TotalSlot slot_;
+    bool recorded_ = false;
+};
+
 // Enqueue the planner kernels and the sort / merge kernels of a plan.  keys
 // (and values) in kb / vb; temp holds the layout for capacity cap, the arrays
-// `limit` keys: offsets that end past either are invalid.
+// `limit` keys: offsets that end past either are invalid.  `total` (or NULL)
+// takes the last offset.
 bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bufs vb, char *temp, uint64_t cap,
-                        uint64_t limit, hipStream_t s)
+                        uint64_t limit, uint64_t *total, hipStream_t s)
 {
     const PlanBounds b = plan_bounds(sp, cap);
     const PlanLayout L = plan_layout(sp, b, cap);
@@ -717,6 +831,10 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
     a.four = sp.four ? 1 : 0;
     a.PM4 = P4;
     a.cap = std::min(cap, limit);
+    TotalReport report(total, s);
+    if (report.failed())
+        return BCF_ERR_NOMEM;
+    a.total = report.word();
     a.status = reinterpret_cast<uint32_t *>(temp + L.status);
     a.bw = reinterpret_cast<uint32_t *>(temp + L.bw);
     a.bg = reinterpret_cast<uint32_t *>(temp + L.bg);
@@ -759,6 +877,7 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
         hipLaunchKernelGGL(k_plan_check, dim3(blocks), dim3(kPlanBlock), 0, s, a, sp.noff);
         BCF_PLAN_TRY(dev(hipGetLastError()));
     }
+    BCF_PLAN_TRY(report.record(s));
     const uint32_t arrays = 2 + PM + P4, first = segs ? 0 : 2;
     if (arrays > first) {  // nothing to count when no pass is planned (a lone run merged in place)
         hipLaunchKernelGGL(k_plan_groups, dim3(arrays - first), dim3(kScanBlock), 0, s, a, first);
@@ -825,7 +944,7 @@ bcf_status plan_and_run(const PlanSpec &sp, const uint64_t *off_dev, Bufs kb, Bu
             prof_end(p);
             BCF_PLAN_TRY(dev(e));
         }
-    return BCF_OK;
+    return report.wait();
 }
 
 // The total of a device offset array (its last entry), read on the host:
@@ -853,8 +972,8 @@ Bufs val_bufs(const uint32_t *in, uint32_t *out, char *temp, uint64_t cap)
 // (sizes are rounded up, and those of merges reserve what either fan-in and an
 // extra copy pass need: 16,000,003 keys in 60 runs, capacity 16,033,536).
 bcf_status planned_call(const PlanSpec &worst, const PlanSpec &actual, const uint64_t *off_dev, const uint32_t *kin,
-                        const uint32_t *vin, uint32_t *kout, uint32_t *vout, uint64_t limit, void *temp,
-                        uint64_t *temp_bytes, hipStream_t s)
+                        const uint32_t *vin, uint32_t *kout, uint32_t *vout, uint64_t limit, uint64_t *total,
+                        void *temp, uint64_t *temp_bytes, hipStream_t s)
 {
     if (!temp) {
         uint64_t n = 0;
@@ -870,7 +989,7 @@ bcf_status planned_call(const PlanSpec &worst, const PlanSpec &actual, const uin
     char *tb = static_cast<char *>(temp);
     const Bufs kb = key_bufs(kin, kout, tb);
     const Bufs vb = actual.pairs ? val_bufs(vin, vout, tb, cap) : Bufs{nullptr, nullptr, nullptr};
-    return plan_and_run(actual, off_dev, kb, vb, tb, cap, limit, s);
+    return plan_and_run(actual, off_dev, kb, vb, tb, cap, limit, total, s);
 }
 
 uint64_t seg_group_min(bool pairs, uint64_t knob) { return knob ? knob : group_run_keys(pairs) / 2; }
@@ -897,8 +1016,8 @@ PlanSpec segments_spec(bool pairs, uint32_t nseg)
 }
 
 bcf_status segmented_device(bool pairs, const uint32_t *kin, const uint32_t *vin, uint32_t *kout, uint32_t *vout,
-                            const uint64_t *off, uint32_t nseg, uint64_t limit, void *temp, uint64_t *temp_bytes,
-                            hipStream_t s)
+                            const uint64_t *off, uint32_t nseg, uint64_t limit, uint64_t *total, void *temp,
+                            uint64_t *temp_bytes, hipStream_t s)
 {
     if (!temp_bytes)
         return BCF_ERR_INVALID;
@@ -910,7 +1029,7 @@ bcf_status segmented_device(bool pairs, const uint32_t *kin, const uint32_t *vin
     if (!off)
         return BCF_ERR_INVALID;
     const PlanSpec sp = segments_spec(pairs, nseg);
-    return planned_call(sp, sp, off, kin, vin, kout, vout, limit, temp, temp_bytes, s);
+    return planned_call(sp, sp, off, kin, vin, kout, vout, limit, total, temp, temp_bytes, s);
 }
 
 PlanSpec runs_spec(bool pairs, uint32_t k)
@@ -936,8 +1055,8 @@ PlanSpec reserved(PlanSpec sp)
 }
 
 bcf_status merge_runs_device(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets, uint32_t k,
-                             uint32_t *keys_out, uint32_t *vals_out, uint64_t limit, void *temp, uint64_t *temp_bytes,
-                             hipStream_t s)
+                             uint32_t *keys_out, uint32_t *vals_out, uint64_t limit, uint64_t *total, void *temp,
+                             uint64_t *temp_bytes, hipStream_t s)
 {
     if (!temp_bytes)
         return BCF_ERR_INVALID;
@@ -966,7 +1085,7 @@ bcf_status merge_runs_device(const uint32_t *keys_in, const uint32_t *vals_in, c
         if (plan_need(sp, cap) > *temp_bytes || n > cap)
             return BCF_ERR_TEMP_TOO_SMALL;
         if (n > limit)
-            return BCF_OK;  // as the device check finds it: nothing is written
+            return total ? (*total = n, BCF_OK) : BCF_OK;  // as the device check finds it: nothing is written
         const PlanLayout L = plan_layout(sp, plan_bounds(sp, cap), cap);
         uint32_t *flag_d = reinterpret_cast<uint32_t *>(static_cast<char *>(temp) + L.status + 12);
         uint32_t flag = 0;
@@ -979,7 +1098,8 @@ bcf_status merge_runs_device(const uint32_t *keys_in, const uint32_t *vals_in, c
         if (flag)
             return BCF_ERR_UNSORTED_RUN;
     }
-    return planned_call(worst, sp, run_offsets, keys_in, vals_in, keys_out, vals_out, limit, temp, temp_bytes, s);
+    return planned_call(worst, sp, run_offsets, keys_in, vals_in, keys_out, vals_out, limit, total, temp,
+                        temp_bytes, s);
 }
 
 }  // namespace
@@ -993,17 +1113,17 @@ extern "C" {
 bcf_status bcf_merge_runs(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets, uint32_t k,
                           uint32_t *keys_out, uint32_t *vals_out, void *temp, uint64_t *temp_bytes, void *stream)
 {
-    return merge_runs_device(keys_in, vals_in, run_offsets, k, keys_out, vals_out, kMaxKeys, temp, temp_bytes,
-                             static_cast<hipStream_t>(stream));
+    return merge_runs_device(keys_in, vals_in, run_offsets, k, keys_out, vals_out, kMaxKeys, nullptr, temp,
+                             temp_bytes, static_cast<hipStream_t>(stream));
 }
 
 bcf_status bcf_merge_runs_within(const uint32_t *keys_in, const uint32_t *vals_in, const uint64_t *run_offsets,
-                                 uint32_t k, uint64_t n, uint32_t *keys_out, uint32_t *vals_out, void *temp,
-                                 uint64_t *temp_bytes, void *stream)
+                                 uint32_t k, uint64_t n, uint32_t *keys_out, uint32_t *vals_out, uint64_t *total,
+                                 void *temp, uint64_t *temp_bytes, void *stream)
 {
     if (!temp)
         return BCF_ERR_INVALID;
-    return merge_runs_device(keys_in, vals_in, run_offsets, k, keys_out, vals_out, n, temp, temp_bytes,
+    return merge_runs_device(keys_in, vals_in, run_offsets, k, keys_out, vals_out, n, total, temp, temp_bytes,
                              static_cast<hipStream_t>(stream));
 }
 
@@ -1026,7 +1146,7 @@ bcf_status bcf_segmented_sort_temp(uint64_t n, uint32_t nseg, int pairs, uint64_
 bcf_status bcf_segmented_sort(const uint32_t *keys_in, uint32_t *keys_out, const uint64_t *seg_offsets, uint32_t nseg,
                               void *temp, uint64_t *temp_bytes, void *stream)
 {
-    return segmented_device(false, keys_in, nullptr, keys_out, nullptr, seg_offsets, nseg, kMaxKeys, temp,
+    return segmented_device(false, keys_in, nullptr, keys_out, nullptr, seg_offsets, nseg, kMaxKeys, nullptr, temp,
                             temp_bytes, static_cast<hipStream_t>(stream));
 }
 
@@ -1034,17 +1154,17 @@ bcf_status bcf_segmented_sort_pairs(const uint32_t *keys_in, const uint32_t *val
                                     uint32_t *vals_out, const uint64_t *seg_offsets, uint32_t nseg, void *temp,
                                     uint64_t *temp_bytes, void *stream)
 {
-    return segmented_device(true, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, kMaxKeys, temp,
+    return segmented_device(true, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, kMaxKeys, nullptr, temp,
                             temp_bytes, static_cast<hipStream_t>(stream));
 }
 
 bcf_status bcf_segmented_sort_within(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_out,
                                      uint32_t *vals_out, const uint64_t *seg_offsets, uint32_t nseg, uint64_t n,
-                                     int pairs, void *temp, uint64_t *temp_bytes, void *stream)
+                                     int pairs, uint64_t *total, void *temp, uint64_t *temp_bytes, void *stream)
 {
     if (!temp)
         return BCF_ERR_INVALID;
-    return segmented_device(pairs != 0, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, n, temp,
+    return segmented_device(pairs != 0, keys_in, vals_in, keys_out, vals_out, seg_offsets, nseg, n, total, temp,
                             temp_bytes, static_cast<hipStream_t>(stream));
 }
 
@@ -1106,7 +1226,7 @@ bcf_status bcf_sort_u32_pb(const uint32_t *keys_in, uint32_t *keys_out, uint64_t
     BCF_PLAN_TRY(bcf_distribute_runs(keys_out, seg.data(), s, P, P, pivot_buckets, dist, pieces, nullptr, scr, &sb,
                                      st));
     return plan_and_run(sp, pieces, key_bufs(dist, keys_out, static_cast<char *>(scr)), Bufs{nullptr, nullptr, nullptr},
-                        static_cast<char *>(scr), n, n, st);
+                        static_cast<char *>(scr), n, n, nullptr, st);
 }
 
 }  // extern "C"
