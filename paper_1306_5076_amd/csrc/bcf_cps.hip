@@ -159,9 +159,12 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t lane)
 }
 
 // Phase 1: per-color sums of tile b = [b * tile, min((b + 1) * tile, n)).
+// The number of tiles is an argument here and below, not gridDim.x, which makes
+// the host fill in the kernel's implicit arguments at every launch: calls of up
+// to 10^6 elements are bound by the host's launches (21.4 us a call with gridDim.x, 20.8 so).
 template <bool CF>
 __global__ __launch_bounds__(kThreads) void k_cps_tile_sums(const uint32_t *values, const uint8_t *colors, uint64_t n,
-                                                            uint32_t d, uint64_t tile, uint32_t *sums)
+                                                            uint32_t d, uint64_t tile, uint32_t tiles, uint32_t *sums)
 {
     extern __shared__ uint32_t cnt[];  // kThreads * d counters
     __shared__ uint32_t part[kWaves][kMaxColors];
@@ -211,14 +214,15 @@ __global__ __launch_bounds__(kThreads) void k_cps_tile_sums(const uint32_t *valu
         uint32_t s = 0;
         for (int w = 0; w < kWaves; ++w)
             s += part[w][t];
-        sums[(uint64_t)t * gridDim.x + blockIdx.x] = s;
+        sums[(uint64_t)t * tiles + blockIdx.x] = s;
     }
 }
 
 // Phase 2: work-group c turns the tile sums of color c into exclusive offsets
-// (sums and offsets are color-major, so its loads are consecutive: 9 us for 8192
-// tiles of 16 colors, 15 tile-major).
-constexpr int kScanThreads = 1024;
+// (sums and offsets are color-major, so its loads are consecutive: 4.9 us for 2048
+// tiles of 16 colors, 6.4 tile-major by 256 threads), with as many threads as the
+// tiles need: 1.6 us for 7 tiles of one color, 1.8 with 1024 threads.
+constexpr int kScanThreads = 1024;  // the most
 constexpr int kScanPer = kMaxTiles / kScanThreads;  // consecutive tiles per thread, all loads in flight at once
 
 __global__ __launch_bounds__(kScanThreads) void k_cps_tile_offsets(const uint32_t *sums, uint32_t *offsets,
@@ -254,11 +258,12 @@ __global__ __launch_bounds__(kScanThreads) void k_cps_tile_offsets(const uint32_
 // Phase 3: the colored prefix sums of tile b, seeded with its offsets.
 template <bool CF>
 __global__ __launch_bounds__(kThreads) void k_cps_scan(const uint32_t *values, const uint8_t *colors, uint32_t *out,
-                                                       uint64_t n, uint32_t d, uint64_t tile, const uint32_t *offsets)
+                                                       uint64_t n, uint32_t d, uint64_t tile, uint32_t tiles,
+                                                       const uint32_t *offsets)
 {
     // from the last tile to the first: phase 1 left the end of the input in the
     // last-level cache (8 us of the call at 2^26 elements and 16 colors)
-    const uint32_t bid = gridDim.x - 1 - blockIdx.x;
+    const uint32_t bid = tiles - 1 - blockIdx.x;
     extern __shared__ uint32_t cnt[];  // kThreads * d counters
     __shared__ __align__(16) uint32_t stage_all[kWaves][kStageWords];
     __shared__ uint32_t wtot[kWaves][kMaxColors];
@@ -266,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void k_cps_scan(const uint32_t *values, c
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t / 64;
     const uint64_t lo = (uint64_t)bid * tile, hi = lo + tile < n ? lo + tile : n;
     if (t < d)
-        carry[t] = offsets[(uint64_t)t * gridDim.x + bid];
+        carry[t] = offsets[(uint64_t)t * tiles + bid];
     for (uint64_t page = lo; page < hi; page += kPage) {
         const uint64_t base = page + (uint64_t)t * kPerThread;
         const uint64_t wbase = page + (uint64_t)wave * (64 * kPerThread);
@@ -386,13 +391,18 @@ extern "C" bcf_status bcf_colored_prefix_sums(const uint32_t *values, const uint
     const dim3 grid((uint32_t)tiles), block(kThreads);
     const size_t lds = (size_t)kThreads * d * sizeof(uint32_t);
     if (conflict_free)
-        hipLaunchKernelGGL(k_cps_tile_sums<true>, grid, block, lds, s, values, colors, n, d, tile, sums);
+        hipLaunchKernelGGL(k_cps_tile_sums<true>, grid, block, lds, s, values, colors, n, d, tile, (uint32_t)tiles,
+                           sums);
     else
-        hipLaunchKernelGGL(k_cps_tile_sums<false>, grid, block, lds, s, values, colors, n, d, tile, sums);
-    hipLaunchKernelGGL(k_cps_tile_offsets, dim3(d), dim3(kScanThreads), 0, s, sums, offsets, (uint32_t)tiles, d);
+        hipLaunchKernelGGL(k_cps_tile_sums<false>, grid, block, lds, s, values, colors, n, d, tile, (uint32_t)tiles,
+                           sums);
+    const uint32_t scan_threads = (uint32_t)((tiles + 64 * kScanPer - 1) / (64 * kScanPer) * 64);
+    hipLaunchKernelGGL(k_cps_tile_offsets, dim3(d), dim3(scan_threads), 0, s, sums, offsets, (uint32_t)tiles, d);
     if (conflict_free)
-        hipLaunchKernelGGL(k_cps_scan<true>, grid, block, lds, s, values, colors, out, n, d, tile, offsets);
+        hipLaunchKernelGGL(k_cps_scan<true>, grid, block, lds, s, values, colors, out, n, d, tile,
+                           (uint32_t)tiles, offsets);
     else
-        hipLaunchKernelGGL(k_cps_scan<false>, grid, block, lds, s, values, colors, out, n, d, tile, offsets);
+        hipLaunchKernelGGL(k_cps_scan<false>, grid, block, lds, s, values, colors, out, n, d, tile,
+                           (uint32_t)tiles, offsets);
     return hipGetLastError() == hipSuccess ? BCF_OK : BCF_ERR_DEVICE;
 }
