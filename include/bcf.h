@@ -203,7 +203,9 @@ bcf_status bcf_merge_runs_host(const uint32_t *keys_in, const uint32_t *vals_in,
  * independently (segments of up to 4096 keys in one wave tile, longer ones
  * block-sorted and then merged within the segment; all segments in one
  * block-sort launch per tile kind and one set of launches per merge level).
- * A segment's runs are merged four at a time (bcf_tuning.merge_fan_in).
+ * A segment's runs are merged four at a time (bcf_tuning.merge_fan_in); planned
+ * on the host, key/value segments of at most two runs are merged pairwise below
+ * 2^26 pairs in all.
  *   seg_offsets  DEVICE, nseg+1 entries (u64)
  * Planned on the device, with the temp and capacity conventions of
  * bcf_merge_runs: the temp size does not depend on the tuning.

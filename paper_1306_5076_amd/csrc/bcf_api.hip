@@ -640,6 +640,15 @@ std::vector<uint8_t> seg_fan_ins(uint64_t runs, bool four)
     return fi;
 }
 
+// Key/value segments of at most two runs take one binary step below this many
+// pairs in all: a level of either fan-in is one merge, and the binary kernels'
+// is the shorter one until the chip is full (us, binary / four-way: 34,575 pairs
+// in 20 segments 91.0 / 102.1, 14.2 M in 3000 266.3 / 280.7, 29.4 M in 20,000
+// 517.9 / 535.8, 94.4 M in 20,000 1272.7 / 1263.7).  With more runs the fewer
+// levels win, and keys' four-way items of two runs have a network of their own
+// (22,730 keys 22.7 / 26.1, 34,575 33.2 / 28.1, 171.8 M 1032 / 991).
+constexpr uint64_t kBinaryPairsMaxN = 1ull << 26;
+
 bcf_status plan_segmented(const uint64_t *off, uint32_t nseg, bool pairs, uint64_t gmin_knob, int fan_in_knob,
                           TablePlan &P)
 {
@@ -647,17 +656,23 @@ bcf_status plan_segmented(const uint64_t *off, uint32_t nseg, bool pairs, uint64
     const uint64_t n = off[nseg];
     const uint64_t gmin = group_min_keys(pairs, gmin_knob);
     const uint64_t grun = group_run_keys(pairs);
-    const bool four = fan_in_knob != 2;  // fan-in 4 steps unless the tuning asks for binary ones
     std::vector<uint32_t> ps(nseg, 0);
     std::vector<uint64_t> run0(nseg, kTile);
     std::vector<std::vector<uint8_t>> fan(nseg);
     uint32_t pmax = 0;
+    uint64_t most_runs = 0;
+    for (uint32_t sg = 0; sg < nseg; ++sg) {
+        const uint64_t len = off[sg + 1] - off[sg];
+        if (len > (uint64_t)kTile && len >= gmin)
+            run0[sg] = grun;
+        most_runs = std::max(most_runs, (len + run0[sg] - 1) / run0[sg]);
+    }
+    const bool four =
+        fan_in_knob == 4 || (fan_in_knob == 0 && !(pairs && most_runs <= 2 && n < kBinaryPairsMaxN));
     for (uint32_t sg = 0; sg < nseg; ++sg) {
         const uint64_t len = off[sg + 1] - off[sg];
         if (len == 0)
             continue;
-        if (len > (uint64_t)kTile && len >= gmin)
-            run0[sg] = grun;
         fan[sg] = seg_fan_ins((len + run0[sg] - 1) / run0[sg], four);
         ps[sg] = (uint32_t)fan[sg].size();
         pmax = std::max(pmax, ps[sg]);
