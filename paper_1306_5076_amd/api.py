@@ -367,8 +367,7 @@ def _planned(fname, keys, off, vals, keys_out, vals_out, stream, workspace, merg
     need = ctypes.c_uint64(0)
     size = lib.bcf_merge_runs_temp if merge else lib.bcf_segmented_sort_temp
     check(fname, size(min(n, 0xFFFFFFFF), k, pairs, ctypes.byref(need)))
-    capturing = _capturing(stream)
-    if not capturing and not (workspace is not None and workspace.holds(need.value, keys.device)):
+    if not (workspace is not None and workspace.holds(need.value, keys.device)) and not _capturing(stream):
         # temp for the keys that the offsets cover, which may be few of those
         # there are: the query reads the last offset back and waits for the
         # stream.  A workspace that holds temp for all the keys needs no query.
@@ -387,15 +386,15 @@ def _planned(fname, keys, off, vals, keys_out, vals_out, stream, workspace, merg
     if keys.numel() and k:
         tp = _ptr(temp) or ctypes.c_void_p(1)
         # the last offset: waits for the first launch of the call, and refuses
-        # totals above 2^32 - 1 (in a capture nothing can be waited for)
+        # totals above 2^32 - 1 (in a capture it is not reported)
         total = ctypes.c_uint64(0)
-        report = None if capturing else ctypes.byref(total)
         if merge:
             check(fname, lib.bcf_merge_runs_within(_ptr(keys), _ptr(vals), _ptr(off), k, n, _ptr(keys_out),
-                                                   _ptr(vals_out), report, tp, ctypes.byref(tb), sh))
+                                                   _ptr(vals_out), ctypes.byref(total), tp, ctypes.byref(tb), sh))
         else:
             check(fname, lib.bcf_segmented_sort_within(_ptr(keys), _ptr(vals), _ptr(keys_out), _ptr(vals_out),
-                                                       _ptr(off), k, n, pairs, report, tp, ctypes.byref(tb), sh))
+                                                       _ptr(off), k, n, pairs, ctypes.byref(total), tp,
+                                                       ctypes.byref(tb), sh))
         if total.value > n:
             warnings.warn(f"{fname}: the offsets end at {total.value}, past the {n} keys: nothing was written",
                           RuntimeWarning, stacklevel=3)
