@@ -89,9 +89,9 @@ constexpr int kGroupWaves64 = 4;  // group tiles of 16384 keys
 // 337, 2^23 405 / 397.
 constexpr uint64_t kGroupMinN64 = 6ull << 20;
 
-// One 4096-key tile per work-group of four waves, 16 keys per lane: sorts of at
-// most 2^19 keys leave the chip nearly empty, and one wave with 64 keys per lane
-// takes 53 us for its chain of instructions.
+// One 4096-key tile per work-group of four waves, 16 keys per lane, for sorts of at
+// most kGroupMinN64 keys: a wave with 64 keys per lane takes 53 us for its chain of
+// instructions, which nothing hides where the chip is nearly empty.
 __global__ __launch_bounds__(kSmallThreads) void k_u64_tile_sort(const uint64_t *__restrict__ in,
                                                                  uint64_t *__restrict__ out, uint64_t n)
 {
