@@ -157,7 +157,7 @@ def bench_small(bcf, workloads, torch, dev, n=1 << 16, reps=100, warmup=10):
     times.sort()
     med = times[len(times) // 2]
     return {"n": n, "median_us": round(med, 2), "p10_us": round(times[reps // 10], 2),
-            "Gkeys_per_s": round(n / med / 1e3, 3), "passes": bcf.sort_passes(n)}
+            "Gkeys_per_s": round(n / med / 1e3, 3), "passes": bcf.sort_data_passes(n)}
 
 
 def bench_block_sorts(bcf, workloads, torch, dev, n=1 << 26, reps=5):
@@ -183,7 +183,7 @@ def bench_block_sorts(bcf, workloads, torch, dev, n=1 << 26, reps=5):
             st = bcf.profile_collect()
             bs = st.get("block_sort_keys", {"total_ms": 0.0, "launches": 1})
             res[name] = {"sort_ms": round(ms, 4), "Gkeys_per_s": round(n / ms / 1e6, 3),
-                         "run_keys": bcf.run_keys(), "passes": bcf.sort_passes(n),
+                         "run_keys": bcf.run_keys(), "passes": bcf.sort_data_passes(n),
                          "block_sort_us": round(bs["total_ms"] * 1e3 / max(1, bs["launches"]), 1)}
     return res
 
@@ -207,7 +207,7 @@ def bench_fan_in(bcf, workloads, torch, dev, n=1 << 26, reps=5):
             bcf.profile_enable(False)
             st = bcf.profile_collect()
             res[f"fan_in_{k}"] = {"sort_ms": round(ms, 4), "Gkeys_per_s": round(n / ms / 1e6, 3),
-                                  "passes": bcf.sort_passes(n), "kernels": _kernel_table(st)}
+                                  "passes": bcf.sort_data_passes(n), "kernels": _kernel_table(st)}
     return res
 
 
@@ -605,7 +605,7 @@ def main():
             "distributions": dists,
             "tile_keys": bcf.tile_keys(),
             "run_keys": bcf.run_keys(),
-            "passes_per_sort": bcf.sort_passes(n),
+            "passes_per_sort": bcf.sort_data_passes(n),
         },
         "per_distribution_ms": per_dist,
         "graph_replay": graph_ms,

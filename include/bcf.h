@@ -359,11 +359,15 @@ uint32_t bcf_run_keys(int pairs);
  * of 11.  Each merge pass finds its work split by reading
  * O(log n) key samples and keys, in a small launch before it or (see
  * bcf_tuning.fused_partition) in the merge kernel.
- * Under the default tuning, sorts of at most 2^19 keys or 2^20 pairs merge
- * up to 16 runs of 4096 per pass by ranks instead, in at most two passes; the
- * count returned for them is that of the binary or four-way passes they
- * replace, as for an explicit merge_fan_in. */
+ * Sorts of at most 2^19 keys or 2^20 pairs under the default tuning merge by
+ * ranks instead, which this count leaves out: it is that of the binary or
+ * four-way passes that the ranks replace (see bcf_sort_data_passes). */
 uint32_t bcf_sort_passes(uint64_t n, int pairs);
+
+/* Passes over the data that a sort of n keys makes under the current tuning,
+ * whichever way it merges: bcf_sort_passes, but for sorts that merge by ranks,
+ * up to 16 runs of 4096 per pass, the block sort and one or two rank passes. */
+uint32_t bcf_sort_data_passes(uint64_t n, int pairs);
 
 /*
  * Process-wide tuning knobs (read by every later call; not per stream).

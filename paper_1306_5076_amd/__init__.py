@@ -27,6 +27,7 @@ _API = (
     "tile_keys",
     "run_keys",
     "sort_passes",
+    "sort_data_passes",
     "profile_enable",
     "profile_collect",
     "get_tuning",

@@ -53,6 +53,7 @@ EXPORTED = (
     "bcf_tile_keys",
     "bcf_run_keys",
     "bcf_sort_passes",
+    "bcf_sort_data_passes",
     "bcf_get_tuning",
     "bcf_set_tuning",
     "bcf_profile_enable",
@@ -153,6 +154,8 @@ def load(path: str = LIB_PATH):
     lib.bcf_run_keys.restype = u32
     lib.bcf_sort_passes.argtypes = [u64, ctypes.c_int]
     lib.bcf_sort_passes.restype = u32
+    lib.bcf_sort_data_passes.argtypes = [u64, ctypes.c_int]
+    lib.bcf_sort_data_passes.restype = u32
     lib.bcf_get_tuning.argtypes = [ctypes.POINTER(Tuning)]
     lib.bcf_get_tuning.restype = None
     lib.bcf_set_tuning.argtypes = [ctypes.POINTER(Tuning)]

@@ -37,6 +37,7 @@ __all__ = [
     "tile_keys",
     "run_keys",
     "sort_passes",
+    "sort_data_passes",
     "profile_enable",
     "profile_collect",
     "get_tuning",
@@ -145,8 +146,16 @@ def run_keys(pairs: bool = False) -> int:
 
 
 def sort_passes(n: int, pairs: bool = False) -> int:
-    """Passes over HBM (block sort + merge passes) of a sort of n keys."""
+    """Block sort + binary or four-way merge passes over HBM for n keys: for
+    small sorts, which merge by ranks, the passes that the ranks replace (see
+    :func:`sort_data_passes`)."""
     return int(load().bcf_sort_passes(n, 1 if pairs else 0))
+
+
+def sort_data_passes(n: int, pairs: bool = False) -> int:
+    """Passes over the data (block sort + merge passes of any kind) that a sort
+    of n keys makes."""
+    return int(load().bcf_sort_data_passes(n, 1 if pairs else 0))
 
 
 def sort_u32(keys, out=None, stream=None, workspace=None):

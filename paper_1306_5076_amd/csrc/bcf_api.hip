@@ -825,6 +825,14 @@ uint32_t bcf_sort_passes(uint64_t n, int pairs)
     return 1 + (uint32_t)sort_fan_ins(pairs != 0, n, tuning()).size();
 }
 
+uint32_t bcf_sort_data_passes(uint64_t n, int pairs)
+{
+    uint32_t fan[2];
+    if (n == 0 || !sort_is_small(pairs != 0, n, tuning()))
+        return bcf_sort_passes(n, pairs);
+    return 1 + rank_fan_ins(tiles_of(n), fan);
+}
+
 bcf_status bcf_sort_u32(const uint32_t *keys_in, uint32_t *keys_out, uint64_t n, void *temp,
                         uint64_t *temp_bytes, void *stream)
 {
