@@ -226,7 +226,7 @@ constexpr int kScanThreads = 1024;  // the most
 constexpr int kScanPer = kMaxTiles / kScanThreads;  // consecutive tiles per thread, all loads in flight at once
 
 __global__ __launch_bounds__(kScanThreads) void k_cps_tile_offsets(const uint32_t *sums, uint32_t *offsets,
-                                                                   uint32_t tiles, uint32_t d)
+                                                                   uint32_t tiles)
 {
     __shared__ uint32_t wtot[kScanThreads / 64];
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t / 64, c = blockIdx.x;
@@ -397,7 +397,7 @@ extern "C" bcf_status bcf_colored_prefix_sums(const uint32_t *values, const uint
         hipLaunchKernelGGL(k_cps_tile_sums<false>, grid, block, lds, s, values, colors, n, d, tile, (uint32_t)tiles,
                            sums);
     const uint32_t scan_threads = (uint32_t)((tiles + 64 * kScanPer - 1) / (64 * kScanPer) * 64);
-    hipLaunchKernelGGL(k_cps_tile_offsets, dim3(d), dim3(scan_threads), 0, s, sums, offsets, (uint32_t)tiles, d);
+    hipLaunchKernelGGL(k_cps_tile_offsets, dim3(d), dim3(scan_threads), 0, s, sums, offsets, (uint32_t)tiles);
     if (conflict_free)
         hipLaunchKernelGGL(k_cps_scan<true>, grid, block, lds, s, values, colors, out, n, d, tile,
                            (uint32_t)tiles, offsets);

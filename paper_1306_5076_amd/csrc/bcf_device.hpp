@@ -314,7 +314,6 @@ BCF_HD void oe_single(Lines<false> &t)
 template <int LO, int N, int D>
 BCF_HD void oe_later_pair(Lines<false> &t)
 {
-    constexpr int S = 2 * D;
 #pragma unroll
     for (int o = 0; o < D; ++o) {  // registers o, o + D, o + 2D, ...: position q of the chain
         constexpr int M = N / D;
@@ -402,19 +401,9 @@ BCF_HD void oe_sort_lines(Lines<false> &t)
 
 // The same networks for the 32-bit element kinds, named by the pairs flag.
 template <int D, int DB, bool P>
-__device__ __forceinline__ void half_clean_step(Lines<P> &t)
-{
-    half_clean_step_lines<D, DB>(t);
-}
-template <int D, int DB, bool P>
 __device__ __forceinline__ void half_clean(Lines<P> &t)
 {
     half_clean_lines<D, DB>(t);
-}
-template <int LO, int HI, int R, bool P>
-__device__ __forceinline__ void oe_merge(Lines<P> &t)
-{
-    oe_merge_lines<LO, HI, R>(t);
 }
 template <int LO, int HI, bool P>
 __device__ __forceinline__ void oe_sort(Lines<P> &t)
@@ -556,14 +545,6 @@ template <class L>
 __device__ __forceinline__ void to_strided(L &t, uint32_t *lds, uint32_t lane)
 {
     exchange<1, kLdsStride>(elems(t), lds, kLdsStride * lane, lane);
-}
-
-// BLOCKED -> STRIDED with the positions reversed (position p of the result
-// holds position 4095 - p): write word 68 lane + r, read word
-// 68(63 - r) + 63 - lane (consecutive lanes, consecutive words).
-__device__ __forceinline__ void to_strided_reversed(Lines<false> &t, uint32_t *lds, uint32_t lane)
-{
-    exchange<1, -kLdsStride>(t.k, lds, kLdsStride * lane, kLdsStride * (kLine - 1) + (kWave - 1) - lane);
 }
 
 // ------------------------------------------ half-width transposes (9 KiB LDS)

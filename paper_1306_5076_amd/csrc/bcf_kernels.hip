@@ -366,53 +366,6 @@ __device__ __forceinline__ void store_elems(const Lines<true> &t, uint32_t *kdst
 
 // ----------------------------------------------------------- block sort body
 
-// Round J (1..6) merges pairs of sorted runs of 2^(5+J) positions into runs of
-// 2^(6+J).  Runs alternate direction (bit 6+J of the position set: the merged
-// run is descending), so each pair is a bitonic sequence and a half-cleaner
-// cascade over position bits 5+J .. 0 sorts it.  Bits 5+J .. 6 are register
-// bits in STRIDED layout, where the direction bit is register bit J (a
-// compile-time constant); bits 5 .. 0 are register bits in BLOCKED layout,
-// where the direction bit is lane bit J and is applied by complementing.
-template <int J, bool P>
-__device__ __forceinline__ void merge_round(Lines<P> &t, uint32_t *lds, uint32_t lane)
-{
-    to_strided(t, lds, lane);
-    half_clean<(1 << (J - 1)), (J < 6 ? J : -1), P>(t);
-    to_blocked(t, lds, lane);
-    if constexpr (J < 6)
-        flip(t, lane >> J);
-    half_clean<kLine / 2, -1, P>(t);
-    if constexpr (J < 6)
-        flip(t, lane >> J);
-}
-
-// Sort one wave tile.  On entry the tile is in STRIDED positions as loaded;
-// it is re-read as BLOCKED (lane l owns the 64 keys it loaded), which is only
-// a renaming of positions: the multiset of the tile, and for pairs the
-// tie-break ranks, are what the sort is defined on.  On exit the tile is
-// sorted in STRIDED layout.
-template <bool P>
-__device__ __forceinline__ void sort_tile_blocked(Lines<P> &t, uint32_t *lds, uint32_t lane)
-{
-    // lines: even lanes ascending, odd lanes descending (run direction = bit 6)
-    flip(t, lane);
-    oe_sort<0, kLine - 1, P>(t);
-    flip(t, lane);
-    merge_round<1, P>(t, lds, lane);
-    merge_round<2, P>(t, lds, lane);
-    merge_round<3, P>(t, lds, lane);
-    merge_round<4, P>(t, lds, lane);
-    merge_round<5, P>(t, lds, lane);
-    merge_round<6, P>(t, lds, lane);
-}
-
-template <bool P>
-__device__ __forceinline__ void sort_tile(Lines<P> &t, uint32_t *lds, uint32_t lane)
-{
-    sort_tile_blocked<P>(t, lds, lane);
-    to_strided(t, lds, lane);
-}
-
 // The paper's base case (Sec. 3.1, Algorithm 1): ShearSort of the 64 x 64
 // tile, kept as an alternative to the merge rounds.  The grid's rows are the
 // lines lanes hold in BLOCKED layout, its columns the lines they hold in
@@ -421,8 +374,8 @@ __device__ __forceinline__ void sort_tile(Lines<P> &t, uint32_t *lds, uint32_t l
 // transpose.  log2(64) = 6 iterations of (rows in snake order: odd rows
 // descending, by complementing; columns ascending) leave the grid sorted in
 // snake order except inside rows; a last ascending row sort then orders it
-// row-major.  13 line sorts of 543 comparators and 12 transposes, against
-// 8.5 line sorts' worth of comparators and 12 transposes for the merge rounds.
+// row-major.  13 line sorts and 12 transposes, against one line sort and six merge
+// rounds with 6 transposes (sort_tile_keys, sort_tile_wide).
 // Entry: the loaded STRIDED registers re-read as BLOCKED; exit: BLOCKED.
 template <bool P>
 __device__ __forceinline__ void shear_sort_blocked(Lines<P> &t, uint32_t *lds, uint32_t lane)
@@ -2114,10 +2067,9 @@ __global__ __launch_bounds__(kWave *kMerge4Waves) __attribute__((amdgpu_waves_pe
 // The same two launches for the merges of a table-driven pass (the segmented
 // sort's segments, each with its own runs): a job is one group of four runs
 // anywhere in one of the three buffers, with its own cut records, item slots
-// and cut searches (task_job / item_job map a search or an item slot to its
-// job).  Runs start at any position, so no samples exist: the cut searches
-// read the keys themselves (32-ary rounds for the binary split, 16-ary for
-// the counts).
+// and cut searches (a search finds its job in the list; item_job maps an item
+// slot to its job).  Runs start at any position, so no samples exist: the cut
+// searches read the keys themselves.
 
 struct Merge4Table {
     Bufs kb;
@@ -2173,7 +2125,7 @@ constexpr uint32_t kFewCuts = 1u << 14;
 // 0 also writes its records P[0] and P[J] (a job with no cut to search has
 // one task for that alone).
 template <int LOG>
-__device__ __forceinline__ void cut4_table_task(const Merge4Table &src, uint32_t task, uint32_t lane, uint32_t part)
+__device__ __forceinline__ void cut4_table_task(const Merge4Table &src, uint32_t task, uint32_t lane)
 {
     constexpr uint32_t kLanes = 1u << LOG;
     const bool in_range = task < src.tasks;
@@ -2249,7 +2201,7 @@ __global__ __launch_bounds__(256) void k_cuts4_table(Merge4Table src)
     }
     for (uint32_t wave = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / kWave) + threadIdx.x / kWave);
          kCuts * wave < src.tasks; wave += waves)
-        cut4_table_task<LOG>(src, kCuts * wave + part, lane, part);
+        cut4_table_task<LOG>(src, kCuts * wave + part, lane);
 }
 
 // One item slot of a table pass.
@@ -2533,19 +2485,6 @@ hipError_t launch_rank_merge(const uint32_t *ksrc, const uint32_t *vsrc, uint32_
     else
         hipLaunchKernelGGL((k_rank_merge<false, false>), grid, block, 0, s, src);
     return hipGetLastError();
-}
-
-static uint32_t cu_count()
-{
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0, c = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || c <= 0)
-            c = 256;
-        cus = c;
-    }
-    return (uint32_t)cus;
 }
 
 template <int NW, bool P, class Src>
