@@ -14,6 +14,9 @@
 // separate kernel instantiation so that a counter run (rocprofv3 --pmc
 // SQ_LDS_BANK_CONFLICT SQ_INSTS_LDS) attributes conflict cycles to it.
 // It also times a plain streaming copy to give the achievable HBM rate.
+// With PROBE_PAIRS set it runs 16-byte accesses of two lanes alone instead, on
+// the same banks of different rows, for every second lane: a counter run then
+// shows by dispatch which lanes are serviced together.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -305,6 +308,43 @@ void run_all(std::integer_sequence<int, Ps...>, uint32_t *sink, unsigned long lo
     (run_pattern<Ps>(sink, cyc_d, cyc_h, cus, clk), ...);
 }
 
+// Lanes a and b access 16 bytes at the start of rows 32 words apart.
+template <bool WRITE>
+__global__ __launch_bounds__(64) void pair_b128(uint32_t a, uint32_t b, uint32_t *out)
+{
+    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+    __shared__ __align__(16) uint32_t m[64 * 32];
+    const uint32_t l = threadIdx.x;
+    for (int i = 0; i < 32; ++i)
+        m[64 * i + l] = l;
+    __syncthreads();
+    if (l != a && l != b)
+        return;
+    volatile Quad *p = reinterpret_cast<volatile Quad *>(m + 32 * l);
+    uint32_t s = 0;
+    for (uint32_t i = 0; i < 256; ++i) {
+        if constexpr (WRITE) {
+            *p = Quad{i, l, i, l};
+        } else {
+            const Quad x = *p;
+            s += x.x + x.y + x.z + x.w;
+        }
+    }
+    out[l] = s + m[32 * l];
+}
+
+static void run_pairs(uint32_t *sink)
+{
+    for (uint32_t a : {0u, 5u, 12u, 33u})
+        for (uint32_t b = 0; b < 64; ++b)
+            if (a != b) {
+                hipLaunchKernelGGL(pair_b128<false>, dim3(1), dim3(64), 0, 0, a, b, sink);
+                hipLaunchKernelGGL(pair_b128<true>, dim3(1), dim3(64), 0, 0, a, b, sink);
+            }
+    CHECK(hipGetLastError());
+    CHECK(hipDeviceSynchronize());
+}
+
 int main()
 {
     hipDeviceProp_t prop;
@@ -324,6 +364,11 @@ int main()
     CHECK(hipMalloc(&cyc_d, 16 * 8 * sizeof(unsigned long long)));
     CHECK(hipMemset(cyc_d, 0, 16 * 8 * sizeof(unsigned long long)));
     std::vector<unsigned long long> cyc_h(16 * 8);
+    if (std::getenv("PROBE_PAIRS") != nullptr) {
+        run_pairs(sink);
+        std::printf("done\n");
+        return 0;
+    }
     const bool copy_only = std::getenv("PROBE_COPY_ONLY") != nullptr;
     if (!copy_only)
         run_all(std::make_integer_sequence<int, kPatterns>{}, sink, cyc_d, cyc_h, cus, clk);
