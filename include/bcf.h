@@ -139,8 +139,8 @@ bcf_status bcf_sort_u64(const uint64_t *keys_in, uint64_t *keys_out, uint64_t n,
 /*
  * Merge k sorted runs into one sorted sequence (the paper's merging of sorted
  * sequences larger than on-chip memory, Sec. 3.2, four runs at a time in
- * ceil(log4 k) passes, or pairwise under merge_fan_in 2).  Stable: among equal keys, lower run index first, then
- * earlier position.
+ * ceil(log4 k) passes, or pairwise under merge_fan_in 2).  Stable: among equal
+ * keys, lower run index first, then earlier position.
  *   keys_in      device, run r occupies [run_offsets[r], run_offsets[r+1])
  *   vals_in      device values carried with the keys, or NULL for keys only
  *   run_offsets  DEVICE, k+1 entries (u64)
@@ -345,7 +345,8 @@ uint32_t bcf_tile_keys(void);
  * or bcf_sort_pairs_u32 (pairs = 1) hands to the merge passes under the current
  * tuning: with group tiles one work-group of several waves sorts that many keys
  * in LDS (32768 keys, 16384 pairs); with wave tiles 4096.  Under the default
- * tuning, sorts of at most 2^19 keys use wave tiles (see bcf_tuning). */
+ * tuning, sorts of at most 2^19 keys or 2^20 pairs sort runs of 4096 (see
+ * bcf_tuning). */
 uint32_t bcf_run_keys(int pairs);
 
 /* Passes over the data in HBM of a sort of n keys under the current tuning:
@@ -408,8 +409,14 @@ typedef struct {
                                   (bcf_sort_u32, bcf_sort_pairs_u32 and the int32 / float
                                   forms), of the segmented sorts (device- or host-planned,
                                   keys or pairs), of bcf_merge_runs and of the bucket merge of
-                                  bcf_sort_u32_pb.  0 (default): 2 for sorts of fewer than
-                                  2^24 keys, else 4.  4 or 2: that fan-in at every size.
+                                  bcf_sort_u32_pb.  0 (default): 4, but 2 for sorts of
+                                  fewer than 2^24 keys (key/value sorts: 4) and for host-planned
+                                  key/value segments of at most two runs (below 2^26 pairs in
+                                  all); sorts of at most 2^19 keys or 2^20 pairs merge up to 16
+                                  runs per pass by ranks instead, while block_sort,
+                                  merge_variant, sampled_partition, tile_samples and
+                                  fused_partition are at their defaults too.  4 or 2: that
+                                  fan-in at every size.
                                   Four-way passes of the sorts need sampled_partition (else 2
                                   is used) and end in a binary one where two runs remain */
 } bcf_tuning;

@@ -20,9 +20,11 @@
 //     of word 68r + lane, so every 32-lane half touches 32 distinct banks;
 //     BLOCKED accesses move four consecutive registers at once, 16 bytes at
 //     word 68 lane + r (r a multiple of 4): lane l's first bank is
-//     4l + r mod 32, so any 8 consecutive lanes (one pass of 128 bytes) cover
-//     the 32 banks once.  The lane-dependent part of an address is a base
-//     register and the register-dependent part an immediate offset;
+//     4l + r mod 32, so the 8 consecutive lanes that a write of 16 bytes
+//     services together cover the 32 banks once, and mod 64 the 16 lanes that
+//     a read services together (lanes of every value mod 16) the 64 banks that
+//     reads have.  The lane-dependent part of an address is a base register
+//     and the register-dependent part an immediate offset;
 //   * compare-exchanges only ever happen between two registers of one lane, so
 //     the sorting networks themselves issue no LDS traffic at all.
 #pragma once
@@ -560,7 +562,8 @@ __device__ __forceinline__ void to_strided(L &t, uint32_t *lds, uint32_t lane)
 // 64 x 68.  Accesses stay conflict-free on the measured geometry: 4-byte
 // writes / reads of word 36r + l' (32 consecutive words per half-wave), and
 // 16-byte reads / writes of word 36l' + c, c a multiple of 4 (36 = 4 mod 32:
-// any 8 consecutive lanes cover the 32 banks once).
+// 8 consecutive lanes cover the 32 banks of writes once, 16 lanes of every value
+// mod 16 the 64 banks of reads).
 constexpr int kHalfRows = 32;
 constexpr int kHalfStride = 36;
 constexpr int kHalfLdsWords = 2 * kHalfRows * kHalfStride;  // per wave: 9 KiB

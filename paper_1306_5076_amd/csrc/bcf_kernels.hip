@@ -3,9 +3,10 @@
 //  k_block_sort  -- base case (paper Sec. 3.1): one wave sorts a 64 x 64 tile
 //                   of 4096 keys.  Lines of 64 keys are sorted in registers
 //                   with Batcher's network; the 64 sorted lines are then merged
-//                   in six rounds of bitonic merging whose compare-exchanges
-//                   are all register-local, alternating between the STRIDED
-//                   and BLOCKED layouts through conflict-free LDS transposes.
+//                   in six rounds of bitonic merging: three by moves between
+//                   eight lanes, three whose compare-exchanges are all
+//                   register-local, between layouts that conflict-free LDS
+//                   transposes switch.
 //  k_merge       -- one binary merge pass (paper Sec. 3.2): every wave produces
 //                   4096 consecutive outputs of the merge of two sorted runs.
 //                   The split of its output range between the runs is found by
@@ -18,8 +19,8 @@
 // Both kernels come in a keys-only and a stable key/value form, and in a
 // "regular" form (all runs of one power-of-two length, positions computed
 // arithmetically) and a "table" form (tiles and merge jobs read from
-// descriptor arrays planned on the host, used for merging arbitrary runs and
-// for segmented sorting).
+// descriptor arrays planned on the host or the device, used for merging
+// arbitrary runs and for segmented sorting).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -742,7 +743,10 @@ __device__ __forceinline__ void wave_tile(Lines<P> &a, const SortItem &it, const
     }
 }
 
-// Wave tiles of key/value sorts, and of keys under the ShearSort ablation.
+// Wave tiles of key/value sorts, and of keys under the ShearSort ablation.  At two
+// waves per SIMD 16 to 21 of a key/value tile's registers spill (80 to 96 bytes of
+// scratch per lane).  1500 segments of up to 2^16 pairs: 75 us for these tiles with
+// one wave per SIMD, no spills and transposes in every round, 50 so.
 template <bool P, class Src, bool SHEAR = false>
 __global__ __launch_bounds__(kWave *kWavesPerGroup) __attribute__((amdgpu_waves_per_eu(SHEAR ? 1 : 2))) void k_block_sort(Src src)
 {
@@ -767,8 +771,8 @@ __global__ __launch_bounds__(kWave *kWavesPerGroup) __attribute__((amdgpu_waves_
 
 // Wave tiles of u32 keys: one wave and 9 KiB of LDS per work-group, 64
 // registers of keys, four waves per SIMD.  Bound by VALU instructions, or by
-// the one wave's chain of them when the tiles are few: 3000 keys 16.8 -> 13.1
-// us, the tiles of a 10,000-segment sort 162 -> 116 us.  The grid strides when
+// the one wave's chain of them when the tiles are few: one tile 16.8 -> 13.1 us,
+// the tiles of a 10,000-segment sort 162 -> 98 us.  The grid strides when
 // it is smaller than the tiles (plans made on the device).
 template <class Src>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4))) void k_block_sort_keys(Src src)
@@ -853,10 +857,13 @@ struct TableGroupSrc {
 // Bound by VALU instructions and the transposes of both element halves; at one
 // wave per SIMD (364 registers) neither overlapped the other's waits.  Loads
 // and stores through range-checked buffer resources and conversions one
-// register at a time fit 256 registers, so two groups share a CU; rounds 1..3
-// of the tiles stay out of the LDS.  Sub-tiles and rounds that a ragged group
-// holds only padding for are left out.  Measured: 2^26 pairs 2567 -> 2200 us (of
-// which the kernel 900 before), 1500 segments of up to 2^16 pairs 385 -> 285.
+// register at a time fit 256 registers (the form that reads a tile list spills 4),
+// so two groups share a CU; rounds 1..3 of the tiles stay out of the LDS.
+// Sub-tiles and rounds that a ragged group holds only padding for are left out.
+// Measured: 2^26 pairs 2567 -> 2200 us (the kernel 900 -> 485), 1500 segments of up
+// to 2^16 pairs 385 -> 285.  The networks' exchanges have no bank conflicts; the
+// values' reads by rank go to data-dependent words (0.20 conflict cycles per LDS
+// instruction in all).
 template <int NW, class Src>
 __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(2))) void k_block_sort_group_pairs(Src src)
 {
@@ -900,11 +907,12 @@ __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(2))) 
 // Group tiles of u32 keys: 8 waves sort 32768 keys.  Two work-groups share a
 // CU (72 KiB of LDS and at most 128 registers a lane), so one group's loads,
 // barriers and LDS exchanges overlap the other's networks.  Bound by VALU
-// instructions: 6793 per wave of 4096 keys, issued in 94 % of the cycles
-// (SQ_ACTIVE_INST_VALU over wave cycles at four waves), 0 LDS bank conflicts.
-// Measured at 2^26 keys under the profiler: 445 us with one group per CU,
-// complemented runs and 139 KiB of LDS, 300 us so.  The grid strides when it is smaller than the groups; the
-// trip count is the same for all waves, so every wave reaches every barrier.
+// instructions: 6879 per wave of 4096 keys; SQ_ACTIVE_INST_VALU is 23.4 % of
+// SQ_WAVE_CYCLES, 94 % of the issue cycles with four waves per SIMD, and
+// SQ_LDS_BANK_CONFLICT 0.  At 2^26 keys under the profiler: 445 us with one group
+// per CU, complemented runs and 139 KiB of LDS, 262 us so (median of 16 passes).
+// The grid strides when it is smaller than the groups; the trip count is the
+// same for all waves, so every wave reaches every barrier.
 template <class Src>
 __global__ __launch_bounds__(kWave *kKeyGroupWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_block_sort_group_keys(
     Src src)

@@ -130,6 +130,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_u64_tile_sort(const uint64_t 
 // its sub-tile (odd waves descending, by complementing around the sort), then
 // the group rounds merge across the waves.  Every wave of a work-group reaches
 // the same barriers: waves whose sub-tile lies past the end hold padding only.
+// Two waves per SIMD; 24 registers spill (64 bytes of scratch per lane).
 template <bool NT>
 __global__ __launch_bounds__(kWave *kGroupWaves64) __attribute__((amdgpu_waves_per_eu(2))) void k_u64_block_sort_group(
     const uint64_t *__restrict__ in, uint64_t *__restrict__ out, uint64_t n)
