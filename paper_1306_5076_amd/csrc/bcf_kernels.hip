@@ -747,17 +747,17 @@ __device__ __forceinline__ void wave_tile(Lines<P> &a, const SortItem &it, const
 // waves per SIMD 16 to 21 of a key/value tile's registers spill (80 to 96 bytes of
 // scratch per lane).  1500 segments of up to 2^16 pairs: 75 us for these tiles with
 // one wave per SIMD, no spills and transposes in every round, 50 so.
-template <bool P, class Src, bool SHEAR = false>
-__global__ __launch_bounds__(kWave *kWavesPerGroup) __attribute__((amdgpu_waves_per_eu(SHEAR ? 1 : 2))) void k_block_sort(Src src)
+template <bool P, class Src, bool SHEAR = false, int NW = kWavesPerGroup>
+__global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(SHEAR ? 1 : 2))) void k_block_sort(Src src)
 {
     static_assert(P || SHEAR, "u32 keys take k_block_sort_keys");
     src.resolve();
-    __shared__ __align__(16) uint32_t lds_all[kWavesPerGroup][kLdsWords];
+    __shared__ __align__(16) uint32_t lds_all[NW][kLdsWords];
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     uint32_t *lds = lds_all[wave];
-    const uint32_t G = gridDim.x * kWavesPerGroup;
-    for (uint32_t t = blockIdx.x * kWavesPerGroup + wave; t < src.ntiles; t += G) {
+    const uint32_t G = gridDim.x * NW;
+    for (uint32_t t = blockIdx.x * NW + wave; t < src.ntiles; t += G) {
         const uint32_t ln = opaque(lane);
         const SortItem it = src.get(t);
         Lines<P> a;
@@ -2370,6 +2370,14 @@ static bool device_count(const Src &src)
         return false;
 }
 
+template <int NW, class Src>
+static void launch_pair_tiles(const Src &src, hipStream_t s)
+{
+    const auto kernel = k_block_sort<true, Src, false, NW>;
+    const dim3 grid(spread_blocks(kernel, kWave * NW, ((uint64_t)src.ntiles + NW - 1) / NW)), block(kWave * NW);
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, src);
+}
+
 template <bool P, class Src>
 static hipError_t launch_sort(const Src &src, hipStream_t s, bool shear = false)
 {
@@ -2379,9 +2387,16 @@ static hipError_t launch_sort(const Src &src, hipStream_t s, bool shear = false)
         const dim3 grid(persistent_groups(k_block_sort<P, Src, true>, src.ntiles)), block(kWave * kWavesPerGroup);
         hipLaunchKernelGGL((k_block_sort<P, Src, true>), grid, block, 0, s, src);
     } else if constexpr (P) {
-        const uint64_t need = ((uint64_t)src.ntiles + kWavesPerGroup - 1) / kWavesPerGroup;
-        const dim3 grid(spread_blocks(k_block_sort<true, Src>, kWave * kWavesPerGroup, need)), block(kWave * kWavesPerGroup);
-        hipLaunchKernelGGL((k_block_sort<true, Src>), grid, block, 0, s, src);
+        // Four 2-wave groups fit a CU, so R resident ones hold as many groups as the
+        // chip has SIMDs.  Above R / 2 tiles (a group per CU) and up to R, groups of
+        // four waves put one tile on every SIMD; two 2-wave groups of a CU may share
+        // SIMDs while others stay empty (600 tiles 36.8 / 30.4 us, 1024 37.1 / 31.1;
+        // at 512 27.5 / 30.3 and at 1100 39.3 / 41.9).
+        const uint32_t resident = resident_blocks(k_block_sort<true, Src>, kWave * kWavesPerGroup, ~0u);
+        if (!device_count(src) && src.ntiles > resident / 2 && src.ntiles <= resident)
+            launch_pair_tiles<4>(src, s);
+        else
+            launch_pair_tiles<kWavesPerGroup>(src, s);
     } else {
         const uint32_t grid =
             device_count(src) ? spread_blocks(k_block_sort_keys<Src>, kWave, src.ntiles) : src.ntiles;
