@@ -747,10 +747,10 @@ public:
     TotalReport &operator=(const TotalReport &) = delete;
     ~TotalReport()
     {
-        if (!word_)
-            return;
         if (launched_)
             (void)read();  // a word still to be written is not given back
+        if (!word_)
+            return;
         {
             const std::lock_guard<std::mutex> hold(g_total_mu);
             for (uint64_t *&w : g_total)
@@ -762,15 +762,14 @@ public:
     }
     uint64_t *word() const { return word_; }
     bool failed() const { return out_ && !word_; }
-    void launched() { launched_ = true; }
+    void launched() { launched_ = word_ != nullptr; }
     // After the call's launches: the total, refused when no call takes it.
     bcf_status wait()
     {
         if (!out_)
             return BCF_OK;
-        const hipError_t e = read();
         launched_ = false;
-        if (e != hipSuccess)
+        if (!read())
             return BCF_ERR_DEVICE;
         return *out_ > kMaxKeys ? BCF_ERR_INVALID : BCF_OK;
     }
@@ -779,21 +778,27 @@ private:
     // No total that a call takes: offsets that do end so are told by the stream
     // being done with the word as it is.
     static constexpr uint64_t kUnwritten = ~0ull;
-    hipError_t read()
+    bool read()
     {
         using clock = std::chrono::steady_clock;
         auto ask = clock::now() + std::chrono::microseconds(200);
         hipError_t e = hipErrorNotReady;
         while ((*out_ = __atomic_load_n(word_, __ATOMIC_ACQUIRE)) == kUnwritten) {
-            if (e != hipErrorNotReady)
-                return e;  // the stream is done, or has failed
+            if (e == hipSuccess)
+                return true;  // the stream is done
+            if (e != hipErrorNotReady) {
+                word_ = nullptr;  // it has failed: the word may still be written, and is left to it
+                return false;
+            }
             if (clock::now() < ask)
                 continue;
             e = hipStreamQuery(s_);
+            if (e == hipErrorNotReady)
+                (void)hipGetLastError();  // no error of a launch
             std::this_thread::yield();
             ask = clock::now() + std::chrono::microseconds(200);
         }
-        return hipSuccess;
+        return true;
     }
     uint64_t *out_, *word_ = nullptr;
     hipStream_t s_;

@@ -110,3 +110,50 @@ def test_captured_calls_take_the_offsets_of_each_replay(kept):
         eager = bcf.segmented_sort(keys, off)
         torch.cuda.synchronize()
         assert torch.equal(eager, out), r
+
+
+def test_threads_and_streams():
+    """Calls of eight threads on streams of their own, behind work that keeps
+    the device busy for longer than the host polls at once: each takes its own
+    total."""
+    import threading
+
+    import torch
+
+    import paper_1306_5076_amd as bcf
+
+    n, k = 40_000, 9
+    rng = np.random.default_rng(8)
+    host = rng.integers(0, 1 << 31, n).astype(np.int32)
+    keys = torch.from_numpy(host).cuda()
+    busy = torch.randint(0, 1 << 30, (1 << 25,), dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(t):
+        try:
+            stream, ws, out = torch.cuda.Stream(), bcf.Workspace(), torch.empty_like(keys)
+            with torch.cuda.stream(stream):
+                for r in range(6):
+                    cut = np.linspace(0, n, k + 1 + t).astype(np.int64)
+                    off = torch.from_numpy(cut).cuda()
+                    bcf.sort_u32(busy)
+                    bcf.segmented_sort(keys, off, keys_out=out, workspace=ws)
+                    want = oracle.segmented_sort(host.view(np.uint32), cut.astype(np.uint64))
+                    if not np.array_equal(out.cpu().numpy().view(np.uint32), want):
+                        failed.append((t, r, "keys"))
+                    off[-1] = (1 << 32) + t
+                    try:
+                        bcf.segmented_sort(keys, off, keys_out=out, workspace=ws)
+                        failed.append((t, r, "accepted"))
+                    except bcf.BcfError:
+                        pass
+        except Exception as e:  # noqa: BLE001
+            failed.append((t, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(8)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
