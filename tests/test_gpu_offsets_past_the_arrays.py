@@ -6,7 +6,7 @@ inside allocated memory, where the guard words show it."""
 import numpy as np
 import pytest
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.filterwarnings("ignore:.*past the:RuntimeWarning")]
 
 GUARD = 1 << 16  # words behind every array: more than any of the totals below run past it
 
